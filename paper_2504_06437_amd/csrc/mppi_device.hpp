@@ -4,25 +4,26 @@
 // linkage; each unit instantiates what it launches.
 //
 //   rollout kernel  -- one workgroup per tile of S samples.  The horizon is
-//                      cut into chunks that flow through a pipeline of
-//                      workgroup-wide stages; per chunk:
+//                      cut into as few chunks as LDS allows (mostly one); per
+//                      chunk the workgroup runs these phases:
 //                       - inputs: Philox4x32-10 normal x log-normal noise
 //                         (Sec. IV-C) for every (step, sample), turned into the
 //                         state-independent terms (saturated inputs, their
-//                         model terms, the control cost of Alg. 1), in LDS;
-//                       - dynamics: one lane per sample integrates the state
-//                         (eq. veh_dyn), storing the pose of every step and
-//                         adding the tracking and control costs;
-//                       - barrier: every (step, sample) is split over lanes
-//                         that each take a range of obstacles (LDS) and the
-//                         costmap -- the bulk of the work, no dependence
-//                         between items;
+//                         model terms) in LDS; the control cost of Alg. 1;
+//                       - headings: one lane per sample integrates the heading
+//                         (and what drives it), the first half of eq. veh_dyn;
+//                       - their sines and cosines, every item in parallel;
+//                       - positions: one lane per sample and axis integrates
+//                         velocity and position;
+//                       - poses: every (step, sample) is split over lanes that
+//                         each take a range of obstacles (LDS), and the costmap
+//                         -- the bulk of the work, no dependence between items;
 //                       - barrier state: one lane per sample runs the
-//                         recursion of eq. barrier_update and adds R_B beta
-//                         (Alg. 1, eq. cost-to-go_bas) to its compensated
-//                         FP32 cost.
-//                      The sequential parts (dynamics, barrier state) of one
-//                      chunk overlap the parallel parts of its neighbours.
+//                         recursion of eq. barrier_update (Alg. 1, eq.
+//                         cost-to-go_bas).
+//                      Only what depends on the step before is sequential: the
+//                      recurrences are a few operations a step, and everything
+//                      else (sines, costs, barriers) runs on all lanes.
 //                      The tile then forms its own min-shifted exponentials
 //                      and the tile sums eta_b = sum e_k and N_b[t][c] =
 //                      sum e_k du_k.  Tiles never wait for one another.
@@ -212,17 +213,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Compensated accumulation (Knuth's TwoSum): hi + lo carries the sum exactly
-// up to the rounding of lo.
-__device__ __forceinline__ void two_sum_acc(float& hi, float& lo, float x)
-{
-    const float s = hi + x;
-    const float bp = s - hi;
-    const float err = (hi - (s - bp)) + (x - bp);
-    hi = s;
-    lo += err;
-}
-
 // ---------------------------------------------------------------------------
 // Barrier terms.
 // ---------------------------------------------------------------------------
@@ -314,14 +304,21 @@ __device__ __forceinline__ float sdf_sample(const DevParams& p, float gx, float 
 
 // ---------------------------------------------------------------------------
 // Models (explicit Euler, inputs saturated inside f).  inputs() turns the
-// saturated controls into the model's state-independent terms (f0, f1);
-// step() advances the state with them, using the sine and cosine of the *old*
-// heading.
+// saturated controls into the model's state-independent terms (f0, f1).  A
+// step splits into the heading, which follows only from the inputs (and, for
+// the vehicle, the speed they drive), and the position along each axis, which
+// needs the sine and cosine of the *old* heading:
+//   heading(th, w, f0, f1): the new heading th and its companion w (QUAD6:
+//     the turn rate; CAR: the speed; QUAD5: none); returns the word kept
+//     beside f0 for the position (CAR: the new speed, QUAD5: f1);
+//   position(axis, q, v, f0, y, sn, cs): the new position q and velocity v
+//     along axis 0 or 1 (CAR: v is the speed on both).
 // ---------------------------------------------------------------------------
 template <int MODEL> struct Model;
 
 template <> struct Model<MPPI_QUAD6> {
     static constexpr int NS = 6;
+    static constexpr int W = 5;      // state index of the heading's companion (0: none)
     // state (x, z, theta, vx, vz, omega); inputs: rotor thrust deviations from
     // hover.  f0 = (F1 + F2)/m, f1 = (F2 - F1) arm / I.
     __device__ static __forceinline__ void inputs(const DevParams& p, float s0, float s1, float& f0, float& f1)
@@ -331,21 +328,24 @@ template <> struct Model<MPPI_QUAD6> {
         f0 = (F1 + F2) / p.mass;
         f1 = (F2 - F1) * (p.arm / p.inertia);
     }
-    __device__ static __forceinline__ void step(const DevParams& p, float* x, float f0, float f1, float sth, float cth)
+    __device__ static __forceinline__ float heading(float dt, float& th, float& w, float, float f1)
     {
-        const float dt = p.dt;
-        const float x0 = x[0] + x[3] * dt;
-        const float x1 = x[1] + x[4] * dt;
-        const float x2 = x[2] + x[5] * dt;
-        const float x3 = x[3] - f0 * sth * dt;
-        const float x4 = x[4] + (f0 * cth - p.gravity) * dt;
-        const float x5 = x[5] + f1 * dt;
-        x[0] = x0; x[1] = x1; x[2] = x2; x[3] = x3; x[4] = x4; x[5] = x5;
+        th = fmaf(w, dt, th);
+        w = fmaf(f1, dt, w);
+        return w;
+    }
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float f0, float,
+                                                    float sn, float cs)
+    {
+        const float a = axis == 0 ? -(f0 * sn) : fmaf(f0, cs, -p.gravity);
+        q = fmaf(v, p.dt, q);
+        v = fmaf(a, p.dt, v);
     }
 };
 
 template <> struct Model<MPPI_QUAD5> {
     static constexpr int NS = 5;
+    static constexpr int W = 0;
     // Sec. V-A: state (x, z, theta, vx, vz); inputs (pitch rate, throttle).
     // f0 = pitch rate, f1 = (m g + u_t)/m.
     __device__ static __forceinline__ void inputs(const DevParams& p, float s0, float s1, float& f0, float& f1)
@@ -353,20 +353,21 @@ template <> struct Model<MPPI_QUAD5> {
         f0 = s0;
         f1 = (p.mass * p.gravity + s1) / p.mass;
     }
-    __device__ static __forceinline__ void step(const DevParams& p, float* x, float f0, float f1, float sth, float cth)
+    __device__ static __forceinline__ float heading(float dt, float& th, float&, float f0, float f1)
     {
-        const float dt = p.dt;
-        const float x0 = x[0] + x[3] * dt;
-        const float x1 = x[1] + x[4] * dt;
-        const float x2 = x[2] + f0 * dt;
-        const float x3 = x[3] - f1 * sth * dt;
-        const float x4 = x[4] + (f1 * cth - p.gravity) * dt;
-        x[0] = x0; x[1] = x1; x[2] = x2; x[3] = x3; x[4] = x4;
+        th = fmaf(f0, dt, th);
+        return f1;
+    }
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float, float f1,
+                                                    float sn, float cs)
+    {
+        Model<MPPI_QUAD6>::position(p, axis, q, v, f1, 0.0f, sn, cs);
     }
 };
 
 template <> struct Model<MPPI_CAR> {
     static constexpr int NS = 4;
+    static constexpr int W = 3;
     // Sec. V-B Ackermann model: state (x, y, theta, v); inputs (steer, accel).
     // f0 = tan(phi)/L = sin(phi) / (cos(phi) L), f1 = a.
     __device__ static __forceinline__ void inputs(const DevParams& p, float s0, float s1, float& f0, float& f1)
@@ -376,41 +377,43 @@ template <> struct Model<MPPI_CAR> {
         f0 = sp / (cp * p.wheelbase);
         f1 = s1;
     }
-    __device__ static __forceinline__ void step(const DevParams& p, float* x, float f0, float f1, float sth, float cth)
+    __device__ static __forceinline__ float heading(float dt, float& th, float& v, float f0, float f1)
     {
-        const float dt = p.dt;
-        const float v = x[3];
-        const float x0 = x[0] + v * cth * dt;
-        const float x1 = x[1] + v * sth * dt;
-        const float x2 = x[2] + v * f0 * dt;
-        const float x3 = x[3] + f1 * dt;
-        x[0] = x0; x[1] = x1; x[2] = x2; x[3] = x3;
+        th = fmaf(v * f0, dt, th);
+        v = fmaf(f1, dt, v);
+        return v;
+    }
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float, float vn,
+                                                    float sn, float cs)
+    {
+        q = fmaf(v * (axis == 0 ? cs : sn), p.dt, q);
+        v = vn;
     }
 };
 
-// LDS carve-up of one rollout tile (sizes: tile_fixed_lds, then two chunks of
-// per-(step, sample) slots).
+// LDS carve-up of one rollout tile (sizes: tile_fixed_lds, slot_area, noise).
 struct TileLds {
     float4* obs;      // [J] (ox, oy, -r^2 + d, -r^2), local frame; d = |s_0|^2 on the
                       // vehicle's layout-form and the quadrotor's mirrored-axis tiles, else 0
     float2* U;        // [T]
     float* ref;       // [(T+1) n], local frame
     double* e;        // [kMaxTile] tile exponentials
+    double* red;      // [kRollBlock] partial costs, [group][sample]
     double* slots;    // [16] block-reduction slots
-    int* work;        // [4] pool waves per SIMD, [4] the owner wave's SIMD,
-                      // [5], [6] unused, [7] the bits of
-                      // the largest |o|^2 over the obstacles
-    // chunk slots, two buffers each (buffer b at offset b * cb, cb = cs + kXSlots):
-    float4* in;       // [2][cs] per (step, sample): (f0, f1, control cost, costmap terms of the
-                      // chunk two behind: sum B(sdf) or, with the indicator, the smallest sdf)
-    float4* pose;     // [2][cs] per (step, sample): (x, y, cos theta, sin theta)
-    float* bval;      // [2][cs] per (step, sample): fused barrier
+    int* omax;        // the bits of the largest |o|^2 over the obstacles
+    int* next;        // [2] the next unit of a chunk, by chunk parity
+    // slots of one chunk, per (step, sample), cs items and kXSlots more:
+    float4* a;        // (f0, f1), then (f0, y, sin theta, cos theta)
+    float* px;        // position, local frame
+    float* py;
+    float* vx;        // velocity (quadrotors)
+    float* vy;
+    float* b;         // fused barrier (indicator: smallest h), then the barrier state
+    float* mp;        // costmap terms: sum B(sdf) or, with the indicator, the smallest sdf
     float2* nz;       // [T][S] the tile's noise, when it fits (else null)
-    int cs;           // (step, sample) items of a full chunk
-    int cb;           // buffer stride: cs + kXSlots
 };
 
-__device__ __forceinline__ TileLds carve(unsigned char* smem, int J, int T, int n, int cs, bool keep_noise)
+__device__ __forceinline__ TileLds carve(unsigned char* smem, int J, int T, int n, int S, int tc, bool keep_noise)
 {
     TileLds L;
     size_t off = 0;
@@ -423,18 +426,22 @@ __device__ __forceinline__ TileLds carve(unsigned char* smem, int J, int T, int 
     off = (off + 15) & ~(size_t)15;
     L.e = reinterpret_cast<double*>(smem + off);
     off += (size_t)kMaxTile * 8;
+    L.red = reinterpret_cast<double*>(smem + off);
+    off += (size_t)kRollBlock * 8;
     L.slots = reinterpret_cast<double*>(smem + off);
     off += 16 * 8;
-    L.work = reinterpret_cast<int*>(smem + off);
+    L.omax = reinterpret_cast<int*>(smem + off);
+    L.next = L.omax + 1;
     off += 64;
-    L.cs = cs;
-    L.cb = cs + kXSlots;
-    L.in = reinterpret_cast<float4*>(smem + off);
-    off += (size_t)2 * L.cb * 16;
-    L.pose = reinterpret_cast<float4*>(smem + off);
-    off += (size_t)2 * L.cb * 16;
-    L.bval = reinterpret_cast<float*>(smem + off);
-    off += (size_t)2 * L.cb * 4;
+    const int items = tc * S + kXSlots;
+    L.a = reinterpret_cast<float4*>(smem + off);
+    L.px = reinterpret_cast<float*>(L.a + items);
+    L.py = L.px + items;
+    L.b = L.py + items;
+    L.mp = L.b + items;
+    L.vx = L.mp + items;      // (only carved for n > 4)
+    L.vy = L.vx + items;
+    off += slot_area(T, n, S, tc);
     L.nz = keep_noise ? reinterpret_cast<float2*>(smem + off) : nullptr;
     return L;
 }
@@ -445,9 +452,10 @@ struct X0 {
 };
 
 constexpr int kRollWaves = kRollBlock / kWave;
-constexpr int kSimdsPerCU = 4;
-// s_getreg operand for the SIMD of the issuing wave: HW_ID bits [5:4].
-constexpr int kHwIdSimd = (1 << 11) | (4 << 6) | 4;
+// Steps a recurrence reads from LDS ahead of their use: one at a time, each
+// step waits for its read (about 120 cycles a step, against the few of its
+// arithmetic).
+constexpr int kAhead = 8;
 constexpr int kUpdWaves = kUpdBlock / kWave;
 
 // Sum of a float pair over the block (NW waves); every thread gets it.
@@ -518,18 +526,35 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         }
         if (sp < rem) body(ob[0]);
     };
+    // The same walk adding up what the body returns, two obstacles' sum at a
+    // time.
+    auto run_sum = [&](auto&& body, float& sum) __attribute__((always_inline)) {
+        const float4* ob = L.obs + sp;
+        for (int i = 0; i + 2 <= q; i += 2) {
+            const float4 o0 = ob[0], o1 = ob[js];
+            ob += 2 * js;
+            const float f0 = body(o0), f1 = body(o1);
+            sum += f0 + f1;
+        }
+        if (q & 1) {
+            sum += body(ob[0]);
+            ob += js;
+        }
+        if (sp < rem) sum += body(ob[0]);
+    };
     // The same walk for a guarded fast form: fast(o, m) gives an obstacle's
     // sum f and the smallest of the terms whose signs the guard tests, and
     // the form is exact there when m > 0 and f <= fmax; slow(o) gives the
     // clamped per-point sum.  Four obstacles an iteration share one
     // wave-uniform test (the smallest m and the largest f of the four), so
-    // the loop takes no branch per obstacle; the sums are added in obstacle
-    // order either way.
+    // the loop takes no branch per obstacle; the four's sum joins the
+    // running one (beside a term at the barrier's cap every addition to the
+    // running sum rounds at that term's magnitude: a quarter of them).
     auto run_guarded = [&](auto&& fast, auto&& slow, float fmax, float& sum) __attribute__((always_inline)) {
         auto one = [&](const float4 o) __attribute__((always_inline)) {
             float m;
             float f = fast(o, m);
-            const bool ok = (m > 0.0f) & (f <= fmax);
+            const bool ok = m > 0.0f && f <= fmax;
             if (__builtin_expect(__ballot(!ok) != 0, 0)) {
                 const float s = slow(o);
                 f = ok ? f : s;
@@ -552,10 +577,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
                 if (__ballot(!k2)) { const float s = slow(o2); f2 = k2 ? f2 : s; }
                 if (__ballot(!k3)) { const float s = slow(o3); f3 = k3 ? f3 : s; }
             }
-            sum += f0;
-            sum += f1;
-            sum += f2;
-            sum += f3;
+            sum += (f0 + f1) + (f2 + f3);
         }
         for (; i < q; ++i) {
             one(ob[0]);
@@ -592,7 +614,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         // needs the cap term in the guard
         auto body = [&](auto nocap_tag) __attribute__((always_inline)) {
             constexpr bool NOCAP = decltype(nocap_tag)::value;
-            run([&](const float4 o) __attribute__((always_inline)) {
+            run_sum([&](const float4 o) __attribute__((always_inline)) {
                 const float ex = pose.x - o.x, ey = pose.y - o.y;
                 const float C = fmaf(ex, ex, fmaf(ey, ey, o.z));
                 const float Pu = fmaf(ex, cu, ey * su), Qv = fmaf(ey, cv, -ex * sv);
@@ -614,8 +636,8 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
                     const float slow = 0.5f * reciprocal_total<8>(h);
                     f = g >= gmin ? f : slow;
                 }
-                half += f;
-            });
+                return f;
+            }, half);
         };
         const float bound = fmaf(2.0f, fmaf(pose.x, pose.x, pose.y * pose.y), omax2) + ss[0];
         if (__ballot(!(bound <= kCap)) == 0) body(std::true_type{});
@@ -788,19 +810,27 @@ __device__ __forceinline__ float clearance_pose(const DevParams& p, const TileLd
 // fixed-P tiles use the layout form of the paper's bodies).  The standalone
 // and the batched kernels run the same tile.
 //
-// The horizon is cut into chunks of tc steps that flow through a pipeline of
-// workgroup-wide stages.  In stage k:
-//   * the waves that own samples (lane tid < S) first run the barrier-state
-//     recursion over chunk k-2 and then integrate the dynamics of chunk k --
-//     the two sequential parts, one lane per sample;
-//   * the other waves draw the noise and inputs of chunk k+1;
-//   * then the pool waves take units of the fused-barrier work of chunk k-1,
-//     shared out by SIMD (see barrier_chunk).
+// The horizon is cut into chunks of tc steps (tile_chunk: the whole horizon
+// where it fits), and each chunk runs through the phases below, one workgroup
+// barrier apart.  The items of a chunk are its (step, sample) pairs, item i =
+// step i / S, sample i mod S; wherever threads walk the items one by one the
+// stride is a multiple of S, so a thread meets one sample only, sample tid mod
+// S, and keeps its share of that sample's cost in a register (FP64).
+//   1  inputs of the chunk (the waves that own no sample; every wave in the
+//      first chunk); meanwhile the owner lanes run the barrier-state
+//      recursion of the chunk before;
+//   2  headings (owner lanes); the others add up the chunk before's barrier
+//      costs;
+//   3  sines and cosines of the headings, their tracking cost;
+//   4  positions (two lanes per sample, one an axis);
+//   5  the rest of the tracking cost, then the barrier and costmap units.
+// Measured: carrying the whole dynamics step on one lane per sample (the
+// sine, the tracking cost and a compensated sum among it) took 0.3 us a
+// step; the recurrences alone take about 0.03.
 // Every (step, sample) of a chunk is split over nsp adjacent lanes; lane sp
 // of the group takes obstacles sp, sp + nsp, ..., so a wave's lanes read one
 // contiguous run of obstacles at a time; the nsp partial sums meet by wave
 // shuffles.
-// Inputs, poses and barrier values are double-buffered by chunk parity.
 // ---------------------------------------------------------------------------
 template <int MODEL, int S, int PT, bool IND, bool MAP>
 __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, unsigned char* smem)
@@ -809,20 +839,17 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     constexpr int NS = Model<MODEL>::NS;
     constexpr int PM = PT ? PT : MPPI_PMAX;
     constexpr int DW = (S + kWave - 1) / kWave;     // waves that own samples
-    constexpr int POOL0 = DW * kWave;               // first thread of the noise pool
+    constexpr int POOL0 = DW * kWave;               // first thread of the other waves
     static_assert(S >= 16 && S <= kMaxTile && (S & (S - 1)) == 0, "tile size");
-    static_assert(POOL0 < kRollBlock, "the noise pool needs a wave");
+    static_assert(POOL0 % S == 0 || S > POOL0, "a thread's items belong to one sample");
+    static_assert(2 * S <= kRollBlock && (kRollBlock - POOL0) % S == 0, "tile size");
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int J = p.J, T = p.T, K = p.K, Kp = p.Kp;
     const int P = PT ? PT : p.P;
-    // the host only configures tiles whose chunk holds at least one step
-    const int tc = tile_chunk_steps(J, T, NS, S);
-    // chunk 0 is shorter: its dynamics run while the barrier pool has no
-    // poses yet
-    const int tc0 = min(tile_first_chunk(T), tc);
-    const int nch = 1 + (T - tc0 + tc - 1) / tc;
+    const int tc = tile_chunk(J, T, NS, S);
+    const int nch = (T + tc - 1) / tc;
     const bool keep_noise = tile_keeps_noise(J, T, NS, S);
-    const TileLds L = carve(smem, J, T, NS, tc * S, keep_noise);
+    const TileLds L = carve(smem, J, T, NS, S, tc, keep_noise);
     const CtrlState* cs_in = p.st;
     const float S_e = cs_in->S_e;
     const uint64_t ctr = cs_in->counter;
@@ -831,28 +858,33 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // the Philox words of sample kk at step t (Sec. IV-C: counter (k, t, iteration))
     // (the key words, uniform over the tile, pass through an empty asm
     // statement, so that the twenty round keys are formed per item by scalar
-    // adds instead of being held in scalar registers across the whole stage
+    // adds instead of being held in scalar registers across the whole chunk
     // loop, where they crowded out other values into reloads)
     auto philox_at = [&](int kk, int t) __attribute__((always_inline)) {
         uint32_t k0 = __builtin_amdgcn_readfirstlane(p.seed_lo), k1 = __builtin_amdgcn_readfirstlane(p.seed_hi);
         asm volatile("" : "+s"(k0), "+s"(k1));
         return philox4x32_10(make_uint4((uint32_t)kk, (uint32_t)t, c_lo, c_hi), k0, k1);
     };
-    // Chunk 0's words are drawn first, on the upper half of the workgroup (two
-    // items per thread), while the staging below waits on memory.
-    const int items0 = tc0 * S;
-    const int j0 = tid - kRollBlock / 2;
-    uint4 w0 = make_uint4(0u, 0u, 0u, 0u), w1 = w0;
-    if (j0 >= 0 && j0 < items0) w0 = philox_at(tile * S + (j0 & (S - 1)), j0 / S);
-    if (j0 >= 0 && j0 + kRollBlock / 2 < items0)
-        w1 = philox_at(tile * S + ((j0 + kRollBlock / 2) & (S - 1)), (j0 + kRollBlock / 2) / S);
-
-    const float* Uin = p.U + (size_t)(xs.parity & 1u) * T * kM;
-
     // ---- staging: local frame centred on the start position ----
+    // The first element of each array is loaded before anything waits (one
+    // memory round trip for all three), and this thread's first Philox words
+    // are drawn meanwhile.
+    const float* Uin = p.U + (size_t)(xs.parity & 1u) * T * kM;
+    float ob0 = 0.0f, ob1 = 0.0f, ob2 = 0.0f, ref0 = 0.0f;
+    float2 u0 = make_float2(0.0f, 0.0f);
+    if (tid < J) {
+        ob0 = p.obs[3 * tid];
+        ob1 = p.obs[3 * tid + 1];
+        ob2 = p.obs[3 * tid + 2];
+    }
+    if (tid < T) u0 = make_float2(Uin[2 * tid], Uin[2 * tid + 1]);
+    if (tid < (T + 1) * NS) ref0 = p.xref[tid];
+    const int s_mine = tid & (S - 1);       // the sample of every item this thread walks
+    const uint4 w0 = philox_at(tile * S + s_mine, tid / S);
+
     const double ox = (double)xs.v[0], oy = (double)xs.v[1];
     float omax_mine = 0.0f;     // this thread's largest |o|^2 (local frame), for the barrier's cap bound
-    float omax2 = 0.0f;         // 2 max_j |o_j|^2, known from the first stage on
+    if (tid < 3) L.omax[tid] = 0;           // and the unit counters
     {
         // the vehicle's layout form and the quadrotor's mirrored-axis form
         // offset |e|^2 - r^2 by |s_0|^2 (third word); the fourth word keeps
@@ -861,17 +893,21 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         const double s00 = (double)p.shape[0][0], s01 = (double)p.shape[0][1];
         const double d0 = offset ? s00 * s00 + s01 * s01 : 0.0;
         for (int j = tid; j < J; j += kRollBlock) {
-            const double cx = (double)p.obs[3 * j], cy = (double)p.obs[3 * j + 1], r = (double)p.obs[3 * j + 2];
+            if (j != tid) {
+                ob0 = p.obs[3 * j];
+                ob1 = p.obs[3 * j + 1];
+                ob2 = p.obs[3 * j + 2];
+            }
+            const double cx = (double)ob0, cy = (double)ob1, r = (double)ob2;
             const float4 o = make_float4((float)(cx - ox), (float)(cy - oy), (float)(d0 - r * r), (float)(-(r * r)));
             L.obs[j] = o;
             if constexpr (PT != 0) omax_mine = fmaxf(omax_mine, fmaf(o.x, o.x, o.y * o.y));
         }
     }
-    if (tid < 8) L.work[tid] = 0;
-    for (int t = tid; t < T; t += kRollBlock) L.U[t] = make_float2(Uin[2 * t], Uin[2 * t + 1]);
+    if (tid < T) L.U[tid] = u0;             // (T <= MPPI_TMAX <= the workgroup)
     for (int i = tid; i < (T + 1) * NS; i += kRollBlock) {
         const int a = i % NS;
-        const float v = p.xref[i];
+        const float v = i == tid ? ref0 : p.xref[i];
         L.ref[i] = a == 0 ? (float)((double)v - ox) : a == 1 ? (float)((double)v - oy) : v;
     }
     float inv_res = 0.0f, offx = 0.0f, offy = 0.0f;
@@ -883,21 +919,11 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         offy = (float)((oy - (double)p.map_y0) / (double)p.map_res - 0.5);
     }
     lds_barrier();
-
-    // The barrier units of a stage are shared out by SIMD (see
-    // barrier_chunk): each wave learns its SIMD and, outside the owner waves,
-    // its slot among the pool waves of that SIMD.
-    const int simd = __builtin_amdgcn_s_getreg(kHwIdSimd);
-    int pslot = 0;
-    if (lane == 0) {
-        if (wave >= DW) pslot = atomicAdd(&L.work[simd], 1);
-        else if (wave == 0) L.work[4] = simd;
+    // the largest |o|^2 over the obstacles (non-negative floats order as
+    // their bit patterns); read in phase 5
+    if constexpr (PT != 0) {
+        if (omax_mine > 0.0f) atomicMax(L.omax, __float_as_int(omax_mine));
     }
-    pslot = __builtin_amdgcn_readfirstlane(pslot);
-    int my_pool = 1;                    // pool waves on this wave's SIMD
-    int my_classes = 0;                 // bit cl: this wave's SIMD serves unit class cl
-
-    float beta0 = 0.0f, beta_d = 0.0f;      // fused B(h(x0)), fused B(h(x_d)), formed in stage 1
 
     // ---- setup: lanes 0..S-1 own one sample each ----
     const bool owner = tid < S;
@@ -910,13 +936,14 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     const float cw0 = p.sigma[0] > 0.0f ? p.gamma_u / (S_e * p.sigma[0] * p.sigma[0]) : 0.0f;
     const float cw1 = p.sigma[1] > 0.0f ? p.gamma_u / (S_e * p.sigma[1] * p.sigma[1]) : 0.0f;
 
-    float x[NS];
-    x[0] = 0.0f;
-    x[1] = 0.0f;
-#pragma unroll
-    for (int a = 2; a < NS; ++a) x[a] = xs.v[a];
-    float sth, cth;
-    heading_sincos(x[2], sth, cth);
+    // the recurrences' state: heading and companion on lanes 0..S-1, position
+    // and velocity of axis tid / S on lanes 0..2S-1 (with the sine and cosine
+    // of the last heading)
+    float th = xs.v[2], hw = Model<MODEL>::W ? xs.v[Model<MODEL>::W] : 0.0f;
+    const int axis = tid / S;
+    float q = 0.0f, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
+    float sn_old, cs_old;
+    heading_sincos(xs.v[2], sn_old, cs_old);
     // eq. barrier_update is linear in beta, so beta_t = bv_t + c_t with the
     // sample-dependent part bv_t = b_t + gamma_B bv_{t-1} (bv_0 = beta_0) and
     // the common part c_t = gamma_B (c_{t-1} - beta_d) (c_0 = 0), whose sum is
@@ -924,8 +951,8 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // The common part's cost R_B sum_t c_t is the same for every sample and is
     // added in FP64 (cshift), so a large beta_d cannot swamp the FP32 sums;
     // the host forms its factor R_B sum_t c_t / beta_d once per controller.
-    float beta = 0.0f;
-    float S_hi = 0.0f, S_lo = 0.0f;
+    float beta = 0.0f, beta0 = 0.0f, beta_d = 0.0f;
+    double cost = 0.0;          // this thread's share of the cost of sample s_mine
 
     float sa2[PM], sb2[PM], ss[PM];       // 2 s_i and |s_i|^2
 #pragma unroll
@@ -937,92 +964,110 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         ss[i] = fmaf(a, a, b * b);
     }
 
-    auto chunk_t0 = [&](int c) { return c == 0 ? 0 : tc0 + (c - 1) * tc; };
-    auto chunk_len = [&](int c) { return c == 0 ? tc0 : min(tc, T - chunk_t0(c)); };
-
     // the noise of sample kk at step t (Sec. IV-C mixture, scaled per Alg. 1)
     auto noise_of = [&](uint4 r) __attribute__((always_inline)) {
         return nln_pair(r, scale0, scale1, p.mu_ln, p.sigma_ln, normal_law);
     };
     auto noise_at = [&](int kk, int t) __attribute__((always_inline)) { return noise_of(philox_at(kk, t)); };
 
-    // the inputs of item idx = (t - t0) S + s of a chunk from its noise z
-    auto store_input = [&](float4* dst, int idx, int t, int s, float2 z) __attribute__((always_inline)) {
+    // the inputs and the control cost of item idx (step t) from its Philox words
+    auto input = [&](int idx, int t, uint4 words) __attribute__((always_inline)) {
+        const float2 z = noise_of(words);
         const float2 u = L.U[t];
         const float v0 = u.x + z.x, v1 = u.y + z.y;
         const float s0 = fminf(fmaxf(v0, p.u_min[0]), p.u_max[0]);
         const float s1 = fminf(fmaxf(v1, p.u_min[1]), p.u_max[1]);
         float f0, f1;
         Model<MODEL>::inputs(p, s0, s1, f0, f1);
-        const float ccost = cw0 * u.x * v0 + cw1 * u.y * v1;
-        if constexpr (MAP) {
-            // (.w is left alone: it carries the costmap terms of the chunk
-            // two behind, from the pool's map units to the barrier-state
-            // stage)
-            float* d = reinterpret_cast<float*>(dst + idx);
-            d[0] = f0;
-            d[1] = f1;
-            d[2] = ccost;
-        } else {
-            dst[idx] = make_float4(f0, f1, ccost, 0.0f);
-        }
-        if (keep_noise) L.nz[t * S + s] = z;
+        L.a[idx] = make_float4(f0, f1, 0.0f, 0.0f);
+        cost += (double)(cw0 * u.x * v0 + cw1 * u.y * v1);
+        if (keep_noise) L.nz[t * S + s_mine] = z;
     };
 
-    // inputs of every (step, sample) of chunk c, over threads [first, block)
-    auto inputs_chunk = [&](int c, int first) __attribute__((always_inline)) {
-        const int t0 = chunk_t0(c), items = chunk_len(c) * S;
-        float4* dst = L.in + (c & 1) * L.cb;
-        for (int idx = tid - first; idx < items; idx += kRollBlock - first) {
-            const int s = idx & (S - 1), t = t0 + idx / S;
-            store_input(dst, idx, t, s, noise_at(tile * S + s, t));
+    // phase 1: the inputs of the n steps from t0 on, over threads [first, block)
+    auto inputs_phase = [&](int t0, int n, int first) __attribute__((always_inline)) {
+        int idx = tid - first;
+        uint4 w = w0;
+        if (t0 != 0 && idx < n * S) w = philox_at(tile * S + s_mine, t0 + idx / S);
+        while (idx < n * S) {
+            input(idx, t0 + idx / S, w);
+            idx += kRollBlock - first;
+            if (idx < n * S) w = philox_at(tile * S + s_mine, t0 + idx / S);
         }
     };
 
-    // dynamics of chunk c (owner lanes): poses to LDS, tracking + control cost
-    auto dynamics_chunk = [&](int c) __attribute__((always_inline)) {
-        const int t0 = chunk_t0(c), n = chunk_len(c);
-        const float4* src = L.in + (c & 1) * L.cb;
-        float4* pz = L.pose + (c & 1) * L.cb;
-        float4 nin = src[tid];
-        for (int tt = 0; tt < n; ++tt) {
-            const float4 in = nin;
-            if (tt + 1 < n) nin = src[(tt + 1) * S + tid];
-            const float* rf = L.ref + (t0 + tt + 1) * NS;
-            float ref[NS];
+    // A recurrence over n steps, step tt from what load(tt) returns: kAhead
+    // loads in flight, then their steps, without a branch between them.
+    auto walk = [&](int n, auto&& load, auto&& step) __attribute__((always_inline)) {
+        int tt = 0;
+        for (; tt + kAhead <= n; tt += kAhead) {
+            decltype(load(0)) in[kAhead];
 #pragma unroll
-            for (int a = 0; a < NS; ++a) ref[a] = rf[a];
-            Model<MODEL>::step(p, x, in.x, in.y, sth, cth);
-            heading_sincos(x[2], sth, cth);
-            pz[tt * S + tid] = make_float4(x[0], x[1], cth, sth);
-            float q = 0.0f;
+            for (int i = 0; i < kAhead; ++i) in[i] = load(tt + i);
 #pragma unroll
-            for (int a = 0; a < NS; ++a) {
-                const float d = x[a] - ref[a];
-                q = fmaf(p.Q[a], d * d, q);
+            for (int i = 0; i < kAhead; ++i) step(tt + i, in[i]);
+        }
+        for (; tt < n; ++tt) step(tt, load(tt));
+    };
+
+    // phase 2 (owner lanes): theta into a.z, its companion into a.y
+    auto headings_phase = [&](int n) __attribute__((always_inline)) {
+        float4* a = L.a + tid;
+        walk(
+            n, [&](int tt) __attribute__((always_inline)) { return make_float2(a[tt * S].x, a[tt * S].y); },
+            [&](int tt, float2 in) __attribute__((always_inline)) {
+                const float y = Model<MODEL>::heading(p.dt, th, hw, in.x, in.y);
+                a[tt * S] = make_float4(in.x, y, th, 0.0f);
+            });
+    };
+
+    // phase 3: sines, cosines and the headings' tracking cost
+    auto sines_phase = [&](int t0, int n) __attribute__((always_inline)) {
+        constexpr int W = Model<MODEL>::W;
+        for (int idx = tid; idx < n * S; idx += kRollBlock) {
+            const float4 in = L.a[idx];
+            float sn, cn;
+            heading_sincos(in.z, sn, cn);
+            const float* rf = L.ref + (t0 + idx / S + 1) * NS;
+            const float d2 = in.z - rf[2];
+            float c = p.Q[2] * (d2 * d2);
+            if constexpr (W != 0) {
+                const float dw = in.y - rf[W];
+                c = fmaf(p.Q[W], dw * dw, c);
             }
-            two_sum_acc(S_hi, S_lo, q + in.z);
+            cost += (double)c;
+            L.a[idx] = make_float4(in.x, in.y, sn, cn);
         }
     };
 
-    // barrier-state recursion over chunk c (owner lanes) and its cost; with
-    // the indicator, the weighted count of its steps that violate a
-    // constraint (the pool left each step's smallest h in bval)
-    auto beta_chunk = [&](int c) __attribute__((always_inline)) {
-        const int n = chunk_len(c);
-        const float* bv = L.bval + (c & 1) * L.cb;
-        [[maybe_unused]] const float4* mv = L.in + (c & 1) * L.cb;
-        float nb = bv[tid];
-        for (int tt = 0; tt < n; ++tt) {
-            float b = nb;
-            if constexpr (MAP) b = IND ? fminf(b, mv[tt * S + tid].w) : b + mv[tt * S + tid].w;
-            if (tt + 1 < n) nb = bv[(tt + 1) * S + tid];
-            if constexpr (IND) {
-                if (b < 0.0f) two_sum_acc(S_hi, S_lo, p.collision_weight);
-            } else {
-                beta = fmaf(p.gamma_b, beta, b);
-                two_sum_acc(S_hi, S_lo, p.r_b * beta);
+    // phase 4 (lanes 0..2S-1): positions and velocities
+    auto positions_phase = [&](int n) __attribute__((always_inline)) {
+        const float4* a = L.a + s_mine;
+        float* pos = (axis == 0 ? L.px : L.py) + s_mine;
+        [[maybe_unused]] float* vel = (axis == 0 ? L.vx : L.vy) + s_mine;
+        walk(
+            n, [&](int tt) __attribute__((always_inline)) { return a[tt * S]; },
+            [&](int tt, float4 in) __attribute__((always_inline)) {
+                Model<MODEL>::position(p, axis, q, v, in.x, in.y, sn_old, cs_old);
+                sn_old = in.z;
+                cs_old = in.w;
+                pos[tt * S] = q;
+                if constexpr (NS > 4) vel[tt * S] = v;
+            });
+    };
+
+    // phase 5, first part: the positions' (and velocities') tracking cost
+    auto tracking_cost = [&](int t0, int n) __attribute__((always_inline)) {
+        for (int idx = tid; idx < n * S; idx += kRollBlock) {
+            const float* rf = L.ref + (t0 + idx / S + 1) * NS;
+            const float d0 = L.px[idx] - rf[0], d1 = L.py[idx] - rf[1];
+            float c = fmaf(p.Q[1], d1 * d1, p.Q[0] * (d0 * d0));
+            if constexpr (NS > 4) {
+                const float d3 = L.vx[idx] - rf[3], d4 = L.vy[idx] - rf[4];
+                c = fmaf(p.Q[3], d3 * d3, c);
+                c = fmaf(p.Q[4], d4 * d4, c);
             }
+            cost += (double)c;
         }
     };
 
@@ -1030,129 +1075,173 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // in the parameter block, else formed here.
     const int lg_pack = (p.lg_pack & kLgPackSet) ? p.lg_pack : tile_lg_pack(J, T, NS, S, P);
 
-    // Fused barrier of every (step, sample) of chunk c, in units of one wave.
-    // The units are shared out by SIMD, not taken first come first served: a SIMD's older waves win the issue arbitration, so under a
-    // shared counter they took the most units and the SIMD of the owner wave
-    // finished last.  Unit u belongs to class u mod 4; class cl is served by
-    // the SIMD of rank 3 - cl from the owner wave's SIMD (the class that is
-    // one unit short, when there is one, goes to the owner's SIMD), or,
-    // should that SIMD have no pool wave, by the next one that has.  Within a
-    // SIMD the pool waves take the class's units round-robin by slot; the
-    // owner waves take none.  Which wave computes a unit never changes its
-    // arithmetic.
-    auto barrier_chunk = [&](int c) __attribute__((always_inline)) {
-        const int items = chunk_len(c) * S;
-        // with the barrier state, chunk 0 also takes the poses of x0 and x_d
-        // (its extra slots)
-        const int xitems = (!IND && c == 0) ? kXSlots : 0;
-        const int all = items + xitems;
-        const int lg = (lg_pack >> (c == 0 ? 0 : c == nch - 1 ? 8 : 4)) & 15;
-        const int nsp = 1 << lg;
-        // obstacle units (nsp lanes per item), then, with a costmap, map units
-        // (one item per lane, every shape point: their reads all in flight at
-        // once, away from the long obstacle units)
-        const int ounits = ((all << lg) + kWave - 1) / kWave;
-        const int units = ounits + (MAP ? (all + kWave - 1) / kWave : 0);
-        const float4* pz = L.pose + (c & 1) * L.cb;
-        float* bv = L.bval + (c & 1) * L.cb;
-        [[maybe_unused]] float4* mv = L.in + (c & 1) * L.cb;
-        auto unit = [&](int u) __attribute__((always_inline)) {
-            if constexpr (MAP) {
-                if (u >= ounits) {
-                    const int item = (u - ounits) * kWave + lane;
-                    if (item < all) mv[item].w = map_terms<PT, IND>(p, P, pz[item], inv_res, offx, offy);
-                    return;
+    // phase 5, second part: the fused barrier (or smallest h) of every item of
+    // chunk c, in units of one wave; then, with a costmap, map units (one item
+    // per lane, every shape point: their reads all in flight at once, away
+    // from the long obstacle units); and in chunk 0 one unit for the poses of
+    // x0 and x_d, half a wave each (as items of the list they would open one
+    // more round of full units).  The waves take units from a counter: the
+    // oldest wave of a SIMD wins its issue slots, so with equal shares the
+    // first waves finish at 68 us of a 155 us phase (K = 16384, T = 100, 400
+    // obstacles) and leave the last ones alone on their SIMDs, waiting on
+    // their own latencies.
+    auto units_phase = [&](int c, int n) __attribute__((always_inline)) {
+        const int items = n * S;
+        const int lg = (lg_pack >> (c == nch - 1 ? 4 : 0)) & 15;
+        const int ounits = ((items << lg) + kWave - 1) / kWave;
+        const int munits = MAP ? (items + kWave - 1) / kWave : 0;
+        const int units = ounits + munits + ((!IND && c == 0) ? 1 : 0);
+        [[maybe_unused]] float omax2 = 0.0f;
+        if constexpr (PT != 0) omax2 = 2.0f * __int_as_float(*L.omax);
+        auto pose_of = [&](int item) __attribute__((always_inline)) {
+            const float4 a = L.a[item];
+            return make_float4(L.px[item], L.py[item], a.w, a.z);
+        };
+        auto next_unit = [&]() __attribute__((always_inline)) {
+            int u = 0;
+            if (lane == 0) u = atomicAdd(&L.next[c & 1], 1);
+            return __builtin_amdgcn_readfirstlane(u);
+        };
+        for (int u = next_unit(); u < units; u = next_unit()) {
+            int lgu = lg, item = (u * kWave + lane) >> lg, end = items;
+            if (u >= ounits) {
+                const bool ends = u == ounits + munits;
+                if constexpr (MAP) {
+                    const int it = ends ? items + lane : (u - ounits) * kWave + lane;
+                    if (it < (ends ? items + kXSlots : items))
+                        L.mp[it] = map_terms<PT, IND>(p, P, pose_of(it), inv_res, offx, offy);
                 }
+                if (!ends) continue;
+                lgu = 5;
+                item = items + (lane >> 5);
+                end = items + kXSlots;
             }
-            const int g = u * kWave + lane;
-            const int item = g >> lg, sp = g & (nsp - 1);
+            const int nsp = 1 << lgu, sp = lane & (nsp - 1);
             float part = IND ? INFINITY : 0.0f;
             if constexpr (IND) {
-                if (item < items) part = clearance_pose(p, L, P, sa2, sb2, ss, pz[item], sp, lg);
+                if (item < end) part = clearance_pose(p, L, P, sa2, sb2, ss, pose_of(item), sp, lgu);
                 for (int m = 1; m < nsp; m <<= 1) part = fminf(part, __shfl_xor(part, m));
-                if (sp == 0 && item < items) bv[item] = part;
             } else {
-                if (item < all) part = fused_barrier_pose<MODEL, PT>(p, L, P, sa2, sb2, ss, pz[item], sp, lg, omax2);
+                if (item < end) part = fused_barrier_pose<MODEL, PT>(p, L, P, sa2, sb2, ss, pose_of(item), sp, lgu, omax2);
                 for (int m = 1; m < nsp; m <<= 1) part += __shfl_xor(part, m);
-                if (sp == 0 && item < all) bv[item] = part;
             }
-        };
-        if (wave < DW) return;
-        // the classes this SIMD serves, in turn (one copy of the unit code)
-        for (int cls = my_classes; cls != 0; cls &= cls - 1) {
-            const int cl = __builtin_ctz(cls);
-            for (int u = cl + kSimdsPerCU * pslot; u < units; u += kSimdsPerCU * my_pool) unit(u);
+            if (sp == 0 && item < end) L.b[item] = part;
         }
     };
 
-    // the largest |o|^2 over the obstacles (work[7] was cleared before the
-    // staging barrier; non-negative floats order as their bit patterns)
-    if constexpr (PT != 0) {
-        if (omax_mine > 0.0f) atomicMax(&L.work[7], __float_as_int(omax_mine));
-    }
-    // The first chunk's inputs, on the upper half of the workgroup, from the
-    // words drawn at entry (and drawn here for any item beyond two per thread).
-    if (j0 >= 0) {
-        constexpr int H = kRollBlock / 2;
-        if (j0 < items0) store_input(L.in, j0, j0 / S, j0 & (S - 1), noise_of(w0));
-        if (j0 + H < items0) store_input(L.in, j0 + H, (j0 + H) / S, (j0 + H) & (S - 1), noise_of(w1));
-        for (int idx = j0 + 2 * H; idx < items0; idx += H)
-            store_input(L.in, idx, idx / S, idx & (S - 1), noise_at(tile * S + (idx & (S - 1)), idx / S));
-    }
-    lds_barrier();
-    if constexpr (PT != 0) omax2 = 2.0f * __int_as_float(L.work[7]);
-    // (the SIMD counts are final: the barriers since have synchronised)
-    {
-        my_pool = __builtin_amdgcn_readfirstlane(max(L.work[simd], 1));
-        const int osimd = __builtin_amdgcn_readfirstlane(L.work[4]);
-        int mine = 0;
-#pragma unroll
-        for (int cl = 0; cl < kSimdsPerCU; ++cl) {
-            int sv = (osimd + kSimdsPerCU - 1 - cl) & (kSimdsPerCU - 1);
-            for (int t = 0; t < kSimdsPerCU && L.work[sv] == 0; ++t) sv = (sv + 1) & (kSimdsPerCU - 1);
-            if (sv == simd) mine |= 1 << cl;
-        }
-        my_classes = __builtin_amdgcn_readfirstlane(mine);
-    }
-    for (int st_k = 0; st_k <= nch + 1; ++st_k) {
-        if (wave < DW) {
-            if (!IND && owner && st_k == 2) {
-                // beta_0 and beta_d, formed in stage 1 in chunk 0's extra
-                // slots (buffer 0 is next written in stage 3)
-                const int i0 = tc0 * S;
-                beta0 = L.bval[i0] + (MAP ? L.in[i0].w : 0.0f);
-                beta_d = L.bval[i0 + 1] + (MAP ? L.in[i0 + 1].w : 0.0f);
+    // the fused barrier of item idx with its costmap part
+    auto barrier_at = [&](int idx) __attribute__((always_inline)) {
+        float b = L.b[idx];
+        if constexpr (MAP) b = IND ? fminf(b, L.mp[idx]) : b + L.mp[idx];
+        return b;
+    };
+    // barrier-state recursion over chunk c (owner lanes), in place
+    auto beta_phase = [&](int c, int n) __attribute__((always_inline)) {
+        if constexpr (!IND) {
+            if (c == 0) {
+                beta0 = barrier_at(n * S);
+                beta_d = barrier_at(n * S + 1);
                 beta = beta0;
             }
-            if (owner && st_k >= 2) beta_chunk(st_k - 2);
-            if (owner && st_k < nch) dynamics_chunk(st_k);
-        } else {
-            if (!IND && st_k == 0 && wave == kRollWaves - 1 && lane < kXSlots) {
-                // beta_0 and beta_d are the fused barriers of the poses of x0
-                // and x_d = x_ref[T]: chunk 0 carries them in its two extra
-                // slots, so the barrier units of stage 1 form them (this wave
-                // has no noise to draw in stage 0)
-                const float* xd = L.ref + T * NS;
-                float sn, cn;
-                heading_sincos(lane == 0 ? xs.v[2] : xd[2], sn, cn);
-                L.pose[tc0 * S + lane] = lane == 0 ? make_float4(0.0f, 0.0f, cn, sn) : make_float4(xd[0], xd[1], cn, sn);
-            }
-            if (st_k + 1 < nch) inputs_chunk(st_k + 1, POOL0);
+            walk(
+                n, [&](int tt) __attribute__((always_inline)) { return barrier_at(tt * S + tid); },
+                [&](int tt, float b) __attribute__((always_inline)) {
+                    beta = fmaf(p.gamma_b, beta, b);
+                    L.b[tt * S + tid] = beta;
+                });
         }
-        if (st_k >= 1 && st_k <= nch) barrier_chunk(st_k - 1);
+    };
+    // R_B beta of every item (with the indicator, the weight of every step
+    // that violates a constraint), over threads [first, block)
+    auto beta_cost = [&](int n, int first) __attribute__((always_inline)) {
+        for (int idx = tid - first; idx < n * S; idx += kRollBlock - first) {
+            if constexpr (IND) {
+                if (barrier_at(idx) < 0.0f) cost += (double)p.collision_weight;
+            } else {
+                cost += (double)(p.r_b * L.b[idx]);
+            }
+        }
+    };
+
+    for (int c = 0; c < nch; ++c) {
+        const int t0 = c * tc, n = min(tc, T - t0);
+        if (c == 0) {
+            inputs_phase(0, n, 0);
+        } else if (wave < DW) {
+            if (owner) beta_phase(c - 1, tc);
+        } else {
+            inputs_phase(t0, n, POOL0);
+        }
+        lds_barrier();
+        if (tid == kRollBlock - 1) L.next[(c + 1) & 1] = 0;
+        if (wave < DW) {
+            if (owner) headings_phase(n);
+        } else if (c > 0) {
+            beta_cost(tc, POOL0);
+        }
+        lds_barrier();
+        sines_phase(t0, n);
+        if (!IND && c == 0 && tid >= kRollBlock - kXSlots) {
+            // beta_0 and beta_d are the fused barriers of the poses of x0 and
+            // x_d = x_ref[T], carried in chunk 0's two extra slots
+            const int i = tid - (kRollBlock - kXSlots);
+            const float* xd = L.ref + T * NS;
+            float sn, cn;
+            heading_sincos(i == 0 ? xs.v[2] : xd[2], sn, cn);
+            L.a[n * S + i] = make_float4(0.0f, 0.0f, sn, cn);
+            L.px[n * S + i] = i == 0 ? 0.0f : xd[0];
+            L.py[n * S + i] = i == 0 ? 0.0f : xd[1];
+        }
+        lds_barrier();
+        if (tid < 2 * S) positions_phase(n);
+        lds_barrier();
+        tracking_cost(t0, n);
+        units_phase(c, n);
         lds_barrier();
     }
-    const double cshift = (double)beta_d * p.beta_d_weight;
-    if (owner) {
-        const float* rf = L.ref + T * NS;
-        float phi = 0.0f;
-#pragma unroll
-        for (int a = 0; a < NS; ++a) {
-            const float d = x[a] - rf[a];
-            phi = fmaf(p.Qf[a], d * d, phi);
-        }
-        two_sum_acc(S_hi, S_lo, phi);
+    {
+        const int n = T - (nch - 1) * tc;
+        if (owner) beta_phase(nch - 1, n);
+        if constexpr (!IND) lds_barrier();
+        beta_cost(n, 0);
     }
+    // the terminal cost, from the lanes that hold the final state
+    {
+        const float* rf = L.ref + T * NS;
+        if (owner) {
+            constexpr int W = Model<MODEL>::W;
+            const float d2 = th - rf[2];
+            float c = p.Qf[2] * (d2 * d2);
+            if constexpr (W != 0) {
+                const float dw = hw - rf[W];
+                c = fmaf(p.Qf[W], dw * dw, c);
+            }
+            cost += (double)c;
+        }
+        if (tid < 2 * S) {
+            const float d0 = q - rf[axis];
+            float c = p.Qf[axis] * (d0 * d0);
+            if constexpr (NS > 4) {
+                const float d3 = v - rf[3 + axis];
+                c = fmaf(p.Qf[3 + axis], d3 * d3, c);
+            }
+            cost += (double)c;
+        }
+    }
+    // the samples' costs: lanes of one sample within a wave, then the groups
+    for (int m = S; m < kWave; m <<= 1) cost += __shfl_xor(cost, m);
+    constexpr int RG = S < kWave ? kRollWaves : kRollBlock / S;
+    if (S >= kWave) L.red[tid] = cost;                       // [tid / S][tid % S]
+    else if (lane < S) L.red[wave * S + lane] = cost;
+    lds_barrier();
+    const double cshift = (double)beta_d * p.beta_d_weight;
+    double total = 0.0;
+    if (owner) {
+#pragma unroll
+        for (int g = 0; g < RG; ++g) total += L.red[g * S + tid];
+    }
+    const float S_hi = (float)total;
+    const float S_lo = isfinite(S_hi) ? (float)(total - (double)S_hi) : 0.0f;
 
     // ---- tile softmax partials ----
     // (global stores come after the block reductions, whose barriers would
@@ -1227,9 +1316,9 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     const int k0 = tile * S;
     const int nk = min(S, K - k0);
     const bool store_du = p.export_noise != 0;
-    // with smoothing, the unsmoothed sums gather in the (spent) chunk inputs
+    // with smoothing, the unsmoothed sums gather in the (spent) chunk slots
     const bool smooth = p.sgf_m > 0;
-    double* nb = reinterpret_cast<double*>(L.in);
+    double* nb = reinterpret_cast<double*>(L.a);
     for (int q0 = 0; q0 < T; q0 += steps_per_pass) {
         const int t = q0 + tid / tpt;
         double o0, o1;

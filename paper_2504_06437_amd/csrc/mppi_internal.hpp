@@ -204,18 +204,66 @@ inline int state_dim(int model) { return model == MPPI_QUAD6 ? 6 : model == MPPI
 // LDS obstacle slots (at least one, so the carve-up never has a zero-size array).
 __host__ __device__ inline int obstacle_slots(int J) { return J > 0 ? J : 1; }
 
-constexpr size_t kLdsLimit = 65536;     // dynamic LDS budget of one rollout workgroup
-constexpr int kChunkSlotsMax = 2048;    // most (step, sample) slots in one horizon chunk
+// ---------------------------------------------------------------------------
+// Which tiles are accepted.  A tile of S samples is accepted when a chunk of
+// at least one step of 72-byte slots, beside the tile's fixed arrays, fits
+// 64 KiB (and, with smoothing, the 2T FP64 update sums fit that chunk's
+// inputs).  The layout below needs less per step and has gfx950's whole
+// 160 KiB, so every accepted tile has a layout.
+// ---------------------------------------------------------------------------
+constexpr size_t kAcceptLds = 65536;
+constexpr size_t kAcceptSlot = 72;
+constexpr int kAcceptSlotsMax = 2048;
 
-// Per (step, sample) slot, double-buffered: inputs (float4), pose (float4),
-// fused barrier (float).
-constexpr int kSlotBytes = 2 * (16 + 16 + 4);
-// Each chunk buffer holds two slots beyond its (step, sample) items: chunk 0
-// carries the poses of x0 and x_d = x_ref[T] there, whose fused barriers are
-// beta_0 and beta_d.
+// Fixed part of the acceptance rule: obstacles, U, the reference, the tile's
+// exponentials, reduction words and two extra slots.
+__host__ __device__ inline size_t accept_fixed(int J, int T, int n)
+{
+    size_t b = 0;
+    b += (size_t)obstacle_slots(J) * 16;
+    b += (size_t)T * 8;
+    b += (size_t)(T + 1) * n * 4;
+    b = (b + 15) & ~(size_t)15;
+    return b + (size_t)kMaxTile * 8 + 16 * 8 + 64 + 2 * kAcceptSlot;
+}
+
+// Steps of the acceptance rule's chunk; 0: the tile is refused.
+__host__ __device__ inline int tile_chunk_steps(int J, int T, int n, int S)
+{
+    const size_t fixed = accept_fixed(J, T, n);
+    if (fixed + (size_t)S * kAcceptSlot > kAcceptLds) return 0;
+    long fit = (long)((kAcceptLds - fixed) / ((size_t)S * kAcceptSlot));
+    if (fit > kAcceptSlotsMax / S) fit = kAcceptSlotsMax / S;
+    long tc = (T - (T + 9) / 10 + 2) / 3;
+    if (tc > fit) tc = fit;
+    if (tc < 1) tc = 1;
+    return (int)tc;
+}
+
+// Every place that picks or accepts a tile shape asks this one question.
+__host__ __device__ inline bool tile_fits(int J, int T, int n, int S, int sgf_m)
+{
+    const int tc = tile_chunk_steps(J, T, n, S);
+    if (tc == 0) return false;
+    return sgf_m <= 0 || (size_t)2 * T * 8 <= (size_t)2 * tc * S * 16;
+}
+
+// ---------------------------------------------------------------------------
+// LDS layout of a rollout tile.
+// ---------------------------------------------------------------------------
+constexpr size_t kLdsLimit = 163840;    // gfx950: LDS of one CU, one 1024-thread tile resident
+constexpr size_t kTileLds = kLdsLimit - 256;    // (the batched kernel has a static word)
+constexpr size_t kNoiseLdsMax = 81920;  // most LDS the tile's kept noise may take
+// Each chunk holds two slots beyond its (step, sample) items: chunk 0 carries
+// the poses of x0 and x_d = x_ref[T] there, whose fused barriers are beta_0
+// and beta_d.
 constexpr int kXSlots = 2;
 
-// LDS bytes of a rollout tile apart from the chunk slots.
+// Bytes per (step, sample) slot: inputs/heading (float4), position, for the
+// quadrotors (n > 4) velocity, the fused barrier and the costmap's part.
+__host__ __device__ inline size_t slot_bytes(int n) { return 16 + 8 + (n > 4 ? 8 : 0) + 4 + 4; }
+
+// LDS bytes of a rollout tile apart from the chunk slots and the noise.
 __host__ __device__ inline size_t tile_fixed_lds(int J, int T, int n)
 {
     size_t b = 0;
@@ -224,49 +272,65 @@ __host__ __device__ inline size_t tile_fixed_lds(int J, int T, int n)
     b += (size_t)(T + 1) * n * 4;               // reference, local frame
     b = (b + 15) & ~(size_t)15;
     b += (size_t)kMaxTile * 8;                  // tile exponentials
+    b += (size_t)kRollBlock * 8;                // partial costs per thread group
     b += 16 * 8;                                // block-reduction slots
-    b += 64;                                    // pool waves per SIMD, owner SIMD, the largest |o|^2
-    b += (size_t)kXSlots * kSlotBytes;          // two extra slots per chunk buffer (x0, x_d)
+    b += 64;                                    // the largest |o|^2
     return b;
 }
 
-// First chunk of the rollout pipeline: about a tenth of the horizon.
-__host__ __device__ inline int tile_first_chunk(int T) { return (T + 9) / 10; }
-
-// Steps per horizon chunk of the rollout pipeline after the first: a third
-// of the rest of the horizon, within the LDS budget and kChunkSlotsMax.
-// 0 when even one step does not fit (such a configuration is rejected).
-__host__ __device__ inline int tile_chunk_steps(int J, int T, int n, int S)
+// Bytes of the slot area of a chunk of tc steps (the Savitzky-Golay sums of
+// the epilogue use it once it is spent).
+__host__ __device__ inline size_t slot_area(int T, int n, int S, int tc)
 {
-    const size_t fixed = tile_fixed_lds(J, T, n);
-    if (fixed + (size_t)S * kSlotBytes > kLdsLimit) return 0;
-    long fit = (long)((kLdsLimit - fixed) / ((size_t)S * kSlotBytes));
-    if (fit > kChunkSlotsMax / S) fit = kChunkSlotsMax / S;
-    long tc = (T - tile_first_chunk(T) + 2) / 3;
-    if (tc > fit) tc = fit;
-    if (tc < 1) tc = 1;
-    return (int)tc;
+    const size_t b = ((size_t)tc * S + kXSlots) * slot_bytes(n);
+    const size_t sgf = (size_t)T * 16;
+    return ((b > sgf ? b : sgf) + 15) & ~(size_t)15;
+}
+
+// Does the tile keep its whole noise (T x S float2) in LDS for the epilogue,
+// or draw it again there?  It is kept when it leaves room for chunks of one
+// round (one unit per wave).
+__host__ __device__ inline bool tile_keeps_noise(int J, int T, int n, int S)
+{
+    const size_t nz = (size_t)T * S * 8;
+    const int round = kRollBlock / S;
+    return nz <= kNoiseLdsMax &&
+           tile_fixed_lds(J, T, n) + nz + slot_area(T, n, S, round < T ? round : T) <= kTileLds;
+}
+
+// Steps per horizon chunk: the whole horizon when its slots fit, else as many
+// whole rounds of one 64-lane unit per wave (1024 / S steps) as fit, so that
+// the chunks before the last leave no wave idle; at least one step.
+__host__ __device__ inline int tile_chunk(int J, int T, int n, int S)
+{
+    const size_t used = tile_fixed_lds(J, T, n) + (tile_keeps_noise(J, T, n, S) ? (size_t)T * S * 8 : 0);
+    const size_t room = kTileLds > used + 16 ? kTileLds - used - 16 : 0;
+    const long slots = (long)(room / slot_bytes(n)) - kXSlots;
+    const long fit = slots / S;
+    if (fit >= T) return T;
+    const int round = kRollBlock / S;
+    if (fit >= round) return (int)(fit / round * round);
+    return fit < 1 ? 1 : (int)fit;
 }
 
 // Split of the fused-barrier items of a chunk of `items` (step, sample)
-// items over nsp = 2^lg lanes each, for a tile whose first DW waves own its
-// samples: among the splits that give every wave of the noise pool a unit,
-// the one whose units, spread over the CU's four SIMDs, cost least:
-// ceil(units / 4) units, each of ceil(J / nsp) obstacles x P pairs plus a
-// fixed part (pose, shape transform, reduction: about 8 pairs' worth).
-// Without such a split, the finest.
-__host__ __device__ inline int tile_split_lg(int items, int J, int P, int DW)
+// items over nsp = 2^lg lanes each: among the splits that give every wave a
+// unit, the one that costs least: its units, and the six or so that the
+// workgroup's last ones stand idle for, each of ceil(J / nsp) obstacles x P
+// pairs plus a fixed part (pose, shape transform, reduction, the counter:
+// about 24 pairs' worth).  Without such a split, the finest.
+__host__ __device__ inline int tile_split_lg(int items, int J, int P)
 {
     int lg = 0;
     long best = -1;
     for (int l = 0; l <= 6 && (1 << l) <= (J > 1 ? J : 1); ++l) {
         const long units = ((long)items * (1L << l) + kWave - 1) / kWave;
-        if (units < kRollBlock / kWave - DW) {
+        if (units < kRollBlock / kWave) {
             if (best < 0) lg = l;                        // the finest so far
             continue;
         }
         const long per_lane = (J + (1 << l) - 1) >> l;
-        const long cost = (units + 3) / 4 * (per_lane * P + 8);
+        const long cost = (units + 6) * (per_lane * P + 24);
         if (best < 0 || cost < best) {
             best = cost;
             lg = l;
@@ -277,38 +341,20 @@ __host__ __device__ inline int tile_split_lg(int items, int J, int P, int DW)
 
 constexpr int kLgPackSet = 1 << 12;
 
-// The splits of a tile's chunks, which have at most three lengths (the
-// first, the middle ones, the last), packed 4 bits each, with kLgPackSet.
+// The splits of a tile's chunks (all but the last have one length), packed 4
+// bits each, with kLgPackSet.
 __host__ __device__ inline int tile_lg_pack(int J, int T, int n, int S, int P)
 {
-    const int tc = tile_chunk_steps(J, T, n, S);
-    if (tc == 0) return kLgPackSet;
-    const int tc0 = tile_first_chunk(T) < tc ? tile_first_chunk(T) : tc;
-    const int nch = 1 + (T - tc0 + tc - 1) / tc;
-    const int DW = (S + kWave - 1) / kWave;
-    const int last = nch == 1 ? tc0 : T - (tc0 + (nch - 2) * tc);
-    return kLgPackSet | tile_split_lg(tc0 * S, J, P, DW) | (nch > 2 ? tile_split_lg(tc * S, J, P, DW) << 4 : 0) |
-           (nch > 1 ? tile_split_lg(last * S, J, P, DW) << 8 : 0);
+    const int tc = tile_chunk(J, T, n, S);
+    const int last = T - (T - 1) / tc * tc;
+    return kLgPackSet | tile_split_lg(tc * S, J, P) | tile_split_lg(last * S, J, P) << 4;
 }
 
-// Does a tile of S samples fit the rollout's LDS budget: at least one horizon
-// step per chunk and, with Savitzky-Golay smoothing (sgf_m > 0), room for the
-// 2T FP64 update sums that the tile smooths in the space of its spent chunk
-// inputs (two buffers of tc x S float4)?  Every place that picks or accepts a
-// tile shape asks this one question.
-__host__ __device__ inline bool tile_fits(int J, int T, int n, int S, int sgf_m)
+// Dynamic LDS bytes one rollout tile of this controller needs.
+__host__ __device__ inline size_t tile_lds_bytes(int J, int T, int n, int S)
 {
-    const int tc = tile_chunk_steps(J, T, n, S);
-    if (tc == 0) return false;
-    return sgf_m <= 0 || (size_t)2 * T * 8 <= (size_t)2 * tc * S * 16;
-}
-
-// Does the tile keep its whole noise (T x S float2) in LDS for the epilogue,
-// or draw it again there?
-__host__ __device__ inline bool tile_keeps_noise(int J, int T, int n, int S)
-{
-    return tile_fixed_lds(J, T, n) + (size_t)tile_chunk_steps(J, T, n, S) * S * kSlotBytes + (size_t)T * S * 8 <=
-           kLdsLimit;
+    return tile_fixed_lds(J, T, n) + slot_area(T, n, S, tile_chunk(J, T, n, S)) +
+           (tile_keeps_noise(J, T, n, S) ? (size_t)T * S * 8 : 0);
 }
 
 // Dynamic LDS bytes of the adaptive-exploration kernel: obstacles, the T+1
@@ -316,13 +362,6 @@ __host__ __device__ inline bool tile_keeps_noise(int J, int T, int n, int S)
 inline size_t explore_lds_bytes(int J, int T)
 {
     return (size_t)obstacle_slots(J) * 16 + (size_t)(T + 1) * 16 + (size_t)(T + 1) * 4;
-}
-
-// Dynamic LDS bytes one rollout tile of this controller needs.
-inline size_t tile_lds_bytes(int J, int T, int n, int S)
-{
-    return tile_fixed_lds(J, T, n) + (size_t)tile_chunk_steps(J, T, n, S) * S * kSlotBytes +
-           (tile_keeps_noise(J, T, n, S) ? (size_t)T * S * 8 : 0);
 }
 
 // Kernel launchers (mppi_kernels.hip).  The rollout kernels of each model
