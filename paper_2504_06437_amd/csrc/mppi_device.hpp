@@ -32,6 +32,7 @@
 // FP32 rounding is relative to the rollout's extent, not the world's.
 #pragma once
 
+#include "mppi_field.hpp"
 #include "mppi_internal.hpp"
 
 #include <math.h>
@@ -202,6 +203,12 @@ __device__ __forceinline__ float block_sum_f(float v, double* slots)
 #pragma unroll
     for (int i = 1; i < NW; ++i) r += (float)slots[i];
     return r;
+}
+
+// A value that is the same on every lane, moved to a scalar register.
+__device__ __forceinline__ float uniform(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 // Workgroup barrier that orders LDS accesses only: global stores issued
@@ -391,6 +398,19 @@ template <> struct Model<MPPI_CAR> {
     }
 };
 
+// A grid of the far field seen from the start position: the cell of a local
+// position (x, y) is (ix + floor(gx), iy + floor(gy)) with gx = x inv + fx
+// (the start's own cell and its place in it, split in FP64, so that a query
+// rounds at the rollout's extent, not the world's).
+struct FieldGrid {
+    int32_t ix, iy, nx, ny, base;
+    float fx, fy, inv;
+    float half;         // cell side / W: grid units to the polynomial's coordinates
+    float iw;           // 1 / W: metres to the polynomial's coordinates
+    float pad[2];
+};
+static_assert(sizeof(FieldGrid) * kFieldLevels <= 192, "LDS of the grids");
+
 // LDS carve-up of one rollout tile (sizes: tile_fixed_lds, slot_area, noise).
 struct TileLds {
     float4* obs;      // [J] (ox, oy, -r^2 + d, -r^2), local frame; d = |s_0|^2 on the
@@ -402,7 +422,10 @@ struct TileLds {
     double* slots;    // [16] block-reduction slots
     int* omax;        // the bits of the largest |o|^2 over the obstacles
     int* next;        // [2] the next unit of a chunk, by chunk parity
-    // slots of one chunk, per (step, sample), cs items and kXSlots more:
+    FieldGrid* grid;  // [kFieldLevels] the far field's grids (no cells: no field)
+    float2* shape;    // [MPPI_PMAX] shape points (for lanes that differ in theirs: the kernel
+                      // arguments lie in host memory, and only scalar reads of them are cached)
+    // slots of one chunk, per (step, sample), and kXSlots more:
     float4* a;        // (f0, f1), then (f0, y, sin theta, cos theta)
     float* px;        // position, local frame
     float* py;
@@ -433,7 +456,11 @@ __device__ __forceinline__ TileLds carve(unsigned char* smem, int J, int T, int 
     L.omax = reinterpret_cast<int*>(smem + off);
     L.next = L.omax + 1;
     off += 64;
-    const int items = tc * S + kXSlots;
+    L.grid = reinterpret_cast<FieldGrid*>(smem + off);
+    off += 192;
+    L.shape = reinterpret_cast<float2*>(smem + off);
+    off += MPPI_PMAX * 8;
+    const int items = tc * (S + kRowPad) + kXSlots;
     L.a = reinterpret_cast<float4*>(smem + off);
     L.px = reinterpret_cast<float*>(L.a + items);
     L.py = L.px + items;
@@ -452,6 +479,9 @@ struct X0 {
 };
 
 constexpr int kRollWaves = kRollBlock / kWave;
+// Most lanes (2^kFieldLgMax) that share an item whose barrier comes from the
+// far field.
+constexpr int kFieldLgMax = 2;
 // Steps a recurrence reads from LDS ahead of their use: one at a time, each
 // step waits for its read (about 120 cycles a step, against the few of its
 // arithmetic).
@@ -480,6 +510,98 @@ __device__ __forceinline__ float2 block_sum_f2(float2 v, double* slots)
     return r;
 }
 
+// The quadrotor's mirrored axis with its middle point at the centre, against
+// one obstacle (see fused_barrier_pose): fast() gives half the sum of 1/h over
+// the seven points as one fraction, exact where m > 0 and f <= fcap; slow()
+// the clamped per-point form.  The shape constants are uniform.
+struct AxisBody {
+    float px, py, csw, snw;             // position; 2 a_0 times the heading
+    float D1, D2, DM, R1, R2, nK1, nK2, fcap, eps;
+
+    __device__ __forceinline__ AxisBody(const float* sa2, const float* ss, float4 pose, float eps_)
+    {
+        const float A0 = sa2[0];
+        px = pose.x;
+        py = pose.y;
+        csw = A0 * pose.z;
+        snw = A0 * pose.w;
+        D1 = uniform(ss[1] - ss[0]);
+        D2 = uniform(ss[2] - ss[0]);
+        DM = uniform(-ss[0]);
+        // The heading projection enters scaled by A0 = 2 a_0: w = A0 e.u,
+        // so pair 0's q is b0^2 - w^2 with no coefficient, and pair i's
+        // is b_i^2 - (A_i / A0)^2 w^2.  (A0 = 0 only for a body whose
+        // points all sit at its centre: then every A_i is 0.)
+        R1 = uniform(A0 != 0.0f ? sa2[1] / A0 : 0.0f);
+        R2 = uniform(A0 != 0.0f ? sa2[2] / A0 : 0.0f);
+        nK1 = uniform(-(R1 * R1));
+        nK2 = uniform(-(R2 * R2));
+        fcap = uniform(0.5f / fmaxf(eps_, 1e-4f));
+        eps = eps_;
+    }
+    // The guard reads the fraction itself: h_m = b0 - a_0^2 is the
+    // smallest c_i, so h_m > 0 and q_i = (c_i - d_i)(c_i + d_i) > 0 put
+    // every h above 0; then f = (1/2) sum 1/h <= 1/(2 gmin) puts every
+    // h at or above gmin.  (A NaN f fails the comparison.)
+    // (the middle point enters as hd = 2 h_m, so that pair 2 and the
+    // middle point meet as b2/q2 + 1/hd = (b2 hd + q2)/(q2 hd))
+    __device__ __forceinline__ float fast(const float4 o, float& m) const
+    {
+        const float ex = px - o.x, ey = py - o.y;
+        const float b0 = fmaf(ex, ex, fmaf(ey, ey, o.z));
+        const float w = fmaf(ex, csw, ey * snw);
+        const float b1 = b0 + D1, b2 = b0 + D2;
+        const float hd = fmaf(2.0f, b0, 2.0f * DM);
+        const float w2 = w * w;
+        const float q0 = fmaf(b0, b0, -w2), q1 = fmaf(b1, b1, nK1 * w2);
+        const float q2 = fmaf(b2, b2, nK2 * w2);
+        const float n01 = fmaf(b0, q1, b1 * q0), d01 = q0 * q1;
+        const float n2m = fmaf(b2, hd, q2), d2m = q2 * hd;
+        m = fminf(fminf(q0, q1), fminf(q2, hd));
+        return fmaf(n01, d2m, n2m * d01) * __builtin_amdgcn_rcpf(d01 * d2m);
+    }
+    __device__ __forceinline__ float slow(const float4 o) const
+    {
+        const float ex = px - o.x, ey = py - o.y;
+        const float b0 = fmaf(ex, ex, fmaf(ey, ey, o.z));
+        const float w = fmaf(ex, csw, ey * snw);
+        const float b1 = b0 + D1, b2 = b0 + D2, hm = b0 + DM;
+        float h[7] = {b0 + w, fmaf(R1, w, b1), fmaf(R2, w, b2), hm, fmaf(-R2, w, b2), fmaf(-R1, w, b1), b0 - w};
+#pragma unroll
+        for (int i = 0; i < 7; ++i) h[i] = clamp_h(h[i], eps);
+        return 0.5f * reciprocal_total<7>(h);
+    }
+    // Four obstacles' sum behind one wave-uniform test (a wave takes the
+    // clamped form of an obstacle only when a lane needs it).
+    __device__ __forceinline__ float four(const float4 o0, const float4 o1, const float4 o2, const float4 o3) const
+    {
+        float m0, m1, m2, m3;
+        float f0 = fast(o0, m0), f1 = fast(o1, m1), f2 = fast(o2, m2), f3 = fast(o3, m3);
+        const bool low = fminf(fminf(m0, m1), fminf(m2, m3)) > 0.0f;
+        const bool ok = low && fmaxf(fmaxf(f0, f1), fmaxf(f2, f3)) <= fcap;
+        if (__builtin_expect(__ballot(!ok) != 0, 0)) {
+            const bool k0 = m0 > 0.0f && f0 <= fcap, k1 = m1 > 0.0f && f1 <= fcap;
+            const bool k2 = m2 > 0.0f && f2 <= fcap, k3 = m3 > 0.0f && f3 <= fcap;
+            if (__ballot(!k0)) { const float s = slow(o0); f0 = k0 ? f0 : s; }
+            if (__ballot(!k1)) { const float s = slow(o1); f1 = k1 ? f1 : s; }
+            if (__ballot(!k2)) { const float s = slow(o2); f2 = k2 ? f2 : s; }
+            if (__ballot(!k3)) { const float s = slow(o3); f3 = k3 ? f3 : s; }
+        }
+        return (f0 + f1) + (f2 + f3);
+    }
+    __device__ __forceinline__ float one(const float4 o) const
+    {
+        float m;
+        float f = fast(o, m);
+        const bool ok = m > 0.0f && f <= fcap;
+        if (__builtin_expect(__ballot(!ok) != 0, 0)) {
+            const float s = slow(o);
+            f = ok ? f : s;
+        }
+        return f;
+    }
+};
+
 // Part of the fused barrier of one pose, lane sp of a group of js = 2^lg
 // lanes: every shape point against obstacles sp, sp + js, sp + 2 js, ...
 // below J (read from LDS).  The costmap terms are formed apart (map_terms).
@@ -494,15 +616,15 @@ __device__ __forceinline__ float2 block_sum_f2(float2 v, double* slots)
 // * quadrotors, every point on the body axis (b = 0): h = |e|^2 - r^2 +
 //   fma(2a, e.u, a^2), two operations a pair; when the points mirror about
 //   the centre (the paper's frame), a mirrored pair takes three operations.
-// The runtime-P tile takes any shape: h = (|e|^2 - r^2) + 2 e.d_i + |d_i|^2
-// with d_i the rotated offset, one add and two FMAs a pair.
+// Any other shape takes the general form (walk_points).
 // (sa2, sb2) = 2 (a_i, b_i), ss = a_i^2 + b_i^2.
 template <int MODEL, int PT>
-__device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const TileLds& L, int P, const float* sa2,
+__device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const TileLds& L, const float* sa2,
                                                     const float* sb2, const float* ss, float4 pose, int sp, int lg,
                                                     float omax2)
 {
-    constexpr int PM = PT ? PT : MPPI_PMAX;
+    static_assert(PT != 0, "the general form is walk_points");
+    constexpr int PM = PT;
     const float eps = p.h_eps;
     const float cs = pose.z, sn = pose.w;
     float acc = 0.0f, acc2 = 0.0f;
@@ -526,64 +648,25 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         }
         if (sp < rem) body(ob[0]);
     };
-    // The same walk adding up what the body returns, two obstacles' sum at a
-    // time.
-    auto run_sum = [&](auto&& body, float& sum) __attribute__((always_inline)) {
-        const float4* ob = L.obs + sp;
-        for (int i = 0; i + 2 <= q; i += 2) {
-            const float4 o0 = ob[0], o1 = ob[js];
-            ob += 2 * js;
-            const float f0 = body(o0), f1 = body(o1);
-            sum += f0 + f1;
-        }
-        if (q & 1) {
-            sum += body(ob[0]);
-            ob += js;
-        }
-        if (sp < rem) sum += body(ob[0]);
-    };
-    // The same walk for a guarded fast form: fast(o, m) gives an obstacle's
-    // sum f and the smallest of the terms whose signs the guard tests, and
-    // the form is exact there when m > 0 and f <= fmax; slow(o) gives the
-    // clamped per-point sum.  Four obstacles an iteration share one
-    // wave-uniform test (the smallest m and the largest f of the four), so
-    // the loop takes no branch per obstacle; the four's sum joins the
-    // running one (beside a term at the barrier's cap every addition to the
-    // running sum rounds at that term's magnitude: a quarter of them).
-    auto run_guarded = [&](auto&& fast, auto&& slow, float fmax, float& sum) __attribute__((always_inline)) {
-        auto one = [&](const float4 o) __attribute__((always_inline)) {
-            float m;
-            float f = fast(o, m);
-            const bool ok = m > 0.0f && f <= fmax;
-            if (__builtin_expect(__ballot(!ok) != 0, 0)) {
-                const float s = slow(o);
-                f = ok ? f : s;
-            }
-            sum += f;
-        };
+    // The same walk adding up what the body returns, four obstacles' sum at a
+    // time, in FP64 (an FP32 running sum rounds at its own magnitude at every
+    // addition: over a hundred obstacles, ten times what their terms round at).
+    auto run_sum = [&](auto&& body, double& sum) __attribute__((always_inline)) {
         const float4* ob = L.obs + sp;
         int i = 0;
         for (; i + 4 <= q; i += 4) {
             const float4 o0 = ob[0], o1 = ob[js], o2 = ob[2 * js], o3 = ob[3 * js];
             ob += 4 * js;
-            float m0, m1, m2, m3;
-            float f0 = fast(o0, m0), f1 = fast(o1, m1), f2 = fast(o2, m2), f3 = fast(o3, m3);
-            const bool ok = (fminf(fminf(m0, m1), fminf(m2, m3)) > 0.0f) & (fmaxf(fmaxf(f0, f1), fmaxf(f2, f3)) <= fmax);
-            if (__builtin_expect(__ballot(!ok) != 0, 0)) {
-                const bool k0 = (m0 > 0.0f) & (f0 <= fmax), k1 = (m1 > 0.0f) & (f1 <= fmax);
-                const bool k2 = (m2 > 0.0f) & (f2 <= fmax), k3 = (m3 > 0.0f) & (f3 <= fmax);
-                if (__ballot(!k0)) { const float s = slow(o0); f0 = k0 ? f0 : s; }
-                if (__ballot(!k1)) { const float s = slow(o1); f1 = k1 ? f1 : s; }
-                if (__ballot(!k2)) { const float s = slow(o2); f2 = k2 ? f2 : s; }
-                if (__ballot(!k3)) { const float s = slow(o3); f3 = k3 ? f3 : s; }
-            }
-            sum += (f0 + f1) + (f2 + f3);
+            const float f0 = body(o0), f1 = body(o1), f2 = body(o2), f3 = body(o3);
+            sum += (double)((f0 + f1) + (f2 + f3));
         }
+        float rest = 0.0f;
         for (; i < q; ++i) {
-            one(ob[0]);
+            rest += body(ob[0]);
             ob += js;
         }
-        if (sp < rem) one(ob[0]);
+        if (sp < rem) rest += body(ob[0]);
+        sum += (double)rest;
     };
     // Pair fractions (the layout forms' fast path).  Two points whose h are
     // c + d and c - d give 1/(c+d) + 1/(c-d) = 2c/(c^2 - d^2); the bodies of
@@ -596,8 +679,8 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
     // takes the clamped per-point form.  `half` sums c/q, half of each
     // fraction.
     const float gmin = fmaxf(eps, 1e-4f);
-    float half = 0.0f;
-    if constexpr (PT != 0 && MODEL == MPPI_CAR) {
+    double half = 0.0;
+    if constexpr (MODEL == MPPI_CAR) {
         static_assert(PT == 8, "vehicle layout: 8 points");
         // point 0 is (a, b); o.z = -r^2 + a^2 + b^2, so C = |e|^2 - r^2 + a^2 +
         // b^2 takes two operations, and with P = 2a e.u, Q = 2b e.v the
@@ -642,7 +725,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         const float bound = fmaf(2.0f, fmaf(pose.x, pose.x, pose.y * pose.y), omax2) + ss[0];
         if (__ballot(!(bound <= kCap)) == 0) body(std::true_type{});
         else body(std::false_type{});
-    } else if constexpr (PT != 0) {
+    } else {
         static_assert(PT == 7, "quadrotor layout: 7 points");
         // The mirrored-axis form: a_{6-i} = -a_i, and |a_0| is the largest
         // |a_i| (the host checks both): pair i shares c_i = |e|^2 - r^2 + a_i^2
@@ -663,47 +746,22 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
             fast = __ballot(!(bound <= kCap)) == 0;
         }
         if (fast) {
-            const float A0 = sa2[0], D1 = ss[1] - ss[0], D2 = ss[2] - ss[0];
-            const float DM = -ss[0];
-            // The heading projection enters scaled by A0 = 2 a_0: w = A0 e.u,
-            // so pair 0's q is b0^2 - w^2 with no coefficient, and pair i's
-            // is b_i^2 - (A_i / A0)^2 w^2.  (A0 = 0 only for a body whose
-            // points all sit at its centre: then every A_i is 0.)
-            const float R1 = A0 != 0.0f ? sa2[1] / A0 : 0.0f, R2 = A0 != 0.0f ? sa2[2] / A0 : 0.0f;
-            const float nK1 = -(R1 * R1), nK2 = -(R2 * R2);
-            const float csw = A0 * cs, snw = A0 * sn;
-            // The guard reads the fraction itself: h_m = b0 - a_0^2 is the
-            // smallest c_i, so h_m > 0 and q_i = (c_i - d_i)(c_i + d_i) > 0 put
-            // every h above 0; then f = (1/2) sum 1/h <= 1/(2 gmin) puts every
-            // h at or above gmin.  (A NaN f fails the comparison.)
-            // (the middle point enters as hd = 2 h_m, so that pair 2 and the
-            // middle point meet as b2/q2 + 1/hd = (b2 hd + q2)/(q2 hd))
-            const float fcap = 0.5f / gmin, DM2 = 2.0f * DM;
-            auto fast_sum = [&](const float4 o, float& m) __attribute__((always_inline)) {
-                const float ex = pose.x - o.x, ey = pose.y - o.y;
-                const float b0 = fmaf(ex, ex, fmaf(ey, ey, o.z));
-                const float w = fmaf(ex, csw, ey * snw);
-                const float b1 = b0 + D1, b2 = b0 + D2;
-                const float hd = fmaf(2.0f, b0, DM2);
-                const float w2 = w * w;
-                const float q0 = fmaf(b0, b0, -w2), q1 = fmaf(b1, b1, nK1 * w2);
-                const float q2 = fmaf(b2, b2, nK2 * w2);
-                const float n01 = fmaf(b0, q1, b1 * q0), d01 = q0 * q1;
-                const float n2m = fmaf(b2, hd, q2), d2m = q2 * hd;
-                m = fminf(fminf(q0, q1), fminf(q2, hd));
-                return fmaf(n01, d2m, n2m * d01) * __builtin_amdgcn_rcpf(d01 * d2m);
-            };
-            auto clamped_sum = [&](const float4 o) __attribute__((always_inline)) {
-                const float ex = pose.x - o.x, ey = pose.y - o.y;
-                const float b0 = fmaf(ex, ex, fmaf(ey, ey, o.z));
-                const float w = fmaf(ex, csw, ey * snw);
-                const float b1 = b0 + D1, b2 = b0 + D2, hm = b0 + DM;
-                float h[7] = {b0 + w, fmaf(R1, w, b1), fmaf(R2, w, b2), hm, fmaf(-R2, w, b2), fmaf(-R1, w, b1), b0 - w};
-#pragma unroll
-                for (int i = 0; i < 7; ++i) h[i] = clamp_h(h[i], eps);
-                return 0.5f * reciprocal_total<7>(h);
-            };
-            run_guarded(fast_sum, clamped_sum, fcap, half);
+            // Four obstacles an iteration share one guard test, so the loop
+            // takes no branch per obstacle.
+            const AxisBody body(sa2, ss, pose, eps);
+            const float4* ob = L.obs + sp;
+            int i = 0;
+            for (; i + 4 <= q; i += 4) {
+                half += (double)body.four(ob[0], ob[js], ob[2 * js], ob[3 * js]);
+                ob += 4 * js;
+            }
+            float rest = 0.0f;
+            for (; i < q; ++i) {
+                rest += body.one(ob[0]);
+                ob += js;
+            }
+            if (sp < rem) rest += body.one(ob[0]);
+            half += (double)rest;
         } else {
             // (on the mirrored-axis tile o.z carries the a_0^2 offset)
             float ssx[PM];
@@ -719,25 +777,257 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
                 reciprocal_sum<PM>(h, acc, acc2);
             });
         }
-    } else {
-        float tx[PM], ty[PM];       // 2 d_i
-#pragma unroll
-        for (int i = 0; i < PM; ++i) {
-            tx[i] = fmaf(sa2[i], cs, -sb2[i] * sn);
-            ty[i] = fmaf(sa2[i], sn, sb2[i] * cs);
-        }
-        run([&](const float4 o) __attribute__((always_inline)) {
-            const float ex = pose.x - o.x, ey = pose.y - o.y;
-            const float ee = fmaf(ex, ex, fmaf(ey, ey, o.z));
-#pragma unroll
-            for (int i = 0; i < PM; ++i) {
-                if (i < P) acc += __builtin_amdgcn_rcpf(clamp_h(fmaf(ex, tx[i], fmaf(ey, ty[i], ee + ss[i])), eps));
-            }
-        });
     }
-    acc += acc2;
-    acc = fmaf(2.0f, half, acc);
+    return (float)(2.0 * half + (double)(acc + acc2));
+}
+
+// The general form of one pose against all obstacles, lane sp of a group of
+// js = 2^lg lanes: any shape, h = (|e|^2 - r^2) + 2 e.d_i + |d_i|^2 with d_i
+// the rotated offset.  Returns its share of sum 1/h or, with IND, the smallest
+// h (the comparison controllers' constraint test, Sec. IV-A's weighted
+// indicator: a pose violates a constraint where some h < 0; +inf without an
+// obstacle).  Four points at a time walk the obstacles: their offsets take 12
+// registers where all 16 took 48 and spilled, and four reciprocals are one.
+template <bool IND>
+__device__ __forceinline__ float walk_points(const DevParams& p, const TileLds& L, int P, float4 pose, int sp, int lg)
+{
+    const int J = p.J, js = 1 << lg;
+    float acc = IND ? INFINITY : 0.0f;
+#pragma unroll 1
+    for (int i0 = 0; i0 < P; i0 += 4) {
+        float tx[4], ty[4], ss[4];      // 2 d_i, |d_i|^2
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = min(i0 + k, P - 1);
+            const float a = p.shape[i][0], b = p.shape[i][1];
+            tx[k] = fmaf(2.0f * a, pose.z, -(2.0f * b) * pose.w);
+            ty[k] = fmaf(2.0f * a, pose.w, (2.0f * b) * pose.z);
+            ss[k] = fmaf(a, a, b * b);
+        }
+        const int np = P - i0;
+        auto h_of = [&](const float4 o, float (&h)[4]) __attribute__((always_inline)) {
+            const float ex = pose.x - o.x, ey = pose.y - o.y;
+            const float ee = fmaf(ex, ex, fmaf(ey, ey, o.w));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) h[k] = fmaf(ex, tx[k], fmaf(ey, ty[k], ee + ss[k]));
+        };
+        const float4* ob = L.obs + sp;
+        for (int j = sp; j < J; j += js, ob += js) {
+            float h[4];
+            h_of(ob[0], h);
+            if constexpr (IND) {
+                acc = fminf(acc, fminf(fminf(h[0], h[1]), fminf(h[2], h[3])));
+            } else {
+                // (a point beyond the last: 1/kHMax, 1e-9)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) h[k] = k < np ? clamp_h(h[k], p.h_eps) : kHMax;
+                acc += reciprocal_total<4>(h);
+            }
+        }
+    }
     return acc;
+}
+
+// ---------------------------------------------------------------------------
+// The fused barrier by the far field (mppi_field.hpp).
+// ---------------------------------------------------------------------------
+// The cell of a local position: its record, the polynomial's coordinates and
+// scale.  ok: the position lies on a grid and the cell's near list is whole.
+struct FieldCell {
+    const float* rec;
+    float u, v, iw;
+    int count;          // near obstacles (0 when not ok)
+    bool ok;
+};
+
+__device__ __forceinline__ FieldCell field_cell(const TileLds& L, const float* cells, float x, float y)
+{
+    FieldCell c{cells, 0.0f, 0.0f, 0.0f, 0, false};
+#pragma unroll
+    for (int l = 0; l < kFieldLevels; ++l) {
+        if (l > 0 && __ballot(!c.ok) == 0) break;
+        const FieldGrid g = L.grid[l];
+        const float gx = fmaf(x, g.inv, g.fx), gy = fmaf(y, g.inv, g.fy);
+        const float flx = floorf(gx), fly = floorf(gy);
+        const float tx = (float)g.ix + flx, ty = (float)g.iy + fly;
+        if (!c.ok && tx >= 0.0f && tx < (float)g.nx && ty >= 0.0f && ty < (float)g.ny) {
+            c.rec = cells + (size_t)(g.base + (int)ty * g.nx + (int)tx) * kFieldWords;
+            c.u = ((gx - flx) - 0.5f) * g.half;
+            c.v = ((gy - fly) - 0.5f) * g.half;
+            c.iw = g.iw;
+            c.ok = true;
+        }
+    }
+    if (c.ok) {
+        c.count = __float_as_int(c.rec[kFieldCoefs]);
+        if (c.count == kFieldFull) {
+            c.ok = false;
+            c.count = 0;
+        }
+    }
+    return c;
+}
+
+// The sum over N points of the cell's polynomial (Horner's rule by rows of
+// falling powers of v; the record is read in that order).  The record comes in
+// three thirds, two in flight: all of it at once, beside seven points' rows,
+// spilled 70 registers.
+template <int N>
+__device__ __forceinline__ float field_far(const float* rec, const float (&u)[N], const float (&v)[N], int n = N)
+{
+    constexpr int kThird = 16;
+    static_assert(kFieldCoefs + 3 == 3 * kThird, "three thirds");
+    const float4* r4 = reinterpret_cast<const float4*>(rec);
+    float c[3 * kThird];
+    auto load = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kThird / 4; ++i) {
+            const float4 w = r4[t * kThird / 4 + i];
+            c[t * kThird + 4 * i] = w.x;
+            c[t * kThird + 4 * i + 1] = w.y;
+            c[t * kThird + 4 * i + 2] = w.z;
+            c[t * kThird + 4 * i + 3] = w.w;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(0);
+    load(1);
+    float acc[N], r[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = c[0];
+    int q = 1;
+#pragma unroll
+    for (int l = kFieldDeg - 1; l >= 0; --l) {
+#pragma unroll
+        for (int k = kFieldDeg - l; k >= 0; --k) {
+            if (q == kThird) load(2);
+#pragma unroll
+            for (int i = 0; i < N; ++i) r[i] = k == kFieldDeg - l ? c[q] : fmaf(r[i], u[i], c[q]);
+            ++q;
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = fmaf(acc[i], v[i], r[i]);
+    }
+    float s = acc[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) s += i < n ? acc[i] : 0.0f;
+    return s;
+}
+
+// Near obstacles 4g .. 4g + 3 of a cell (two list words).
+__device__ __forceinline__ uint2 field_near(const float* rec, int g)
+{
+    return reinterpret_cast<const uint2*>(rec + kFieldCoefs + 1)[g];
+}
+
+// The fused barrier of one pose of the quadrotor's axis body, lane sp of
+// 2^LG: points sp, sp + 2^LG, ... of the far polynomial (the whole body is
+// within the cell's margin) and every 2^LG-th group of four near obstacles.
+// ok: false where the pose has no cell.
+template <int LG>
+__device__ __forceinline__ float field_barrier_axis(const DevParams& p, const TileLds& L, const float* cells,
+                                                    const float* sa2, const float* ss, float4 pose, int sp,
+                                                    float omax2, bool& ok)
+{
+    constexpr int NSP = 1 << LG, N = (7 + NSP - 1) / NSP;
+    const FieldCell c = field_cell(L, cells, pose.x, pose.y);
+    ok = c.ok;
+    float u[N], v[N];
+    const float ch = 0.5f * pose.z * c.iw, sh = 0.5f * pose.w * c.iw;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        float a = sa2[i * NSP];
+#pragma unroll
+        for (int k = 1; k < NSP; ++k)
+            if (i * NSP + k < 7) a = sp == k ? sa2[i * NSP + k] : a;
+        u[i] = fmaf(a, ch, c.u);
+        v[i] = fmaf(a, sh, c.v);
+    }
+    const int mine = (7 - sp + NSP - 1) / NSP;
+    float far = field_far<N>(c.rec, u, v, mine);
+    asm volatile("" : "+v"(far));       // (before the near obstacles: the compiler would hold the coefficients through them)
+    const bool mirrored = p.shape_kind == kShapeMirroredAxis;
+    const float bound = fmaf(2.0f, fmaf(pose.x, pose.x, pose.y * pose.y), omax2) + ss[0];
+    const bool fast = mirrored && sa2[3] == 0.0f && __ballot(c.ok && !(bound <= 1.0e5f)) == 0;
+    const int groups = (c.count + 3) >> 2;
+    float near = 0.0f;
+    if (fast) {
+        const AxisBody body(sa2, ss, pose, p.h_eps);
+        float half = 0.0f;
+        for (int g = sp; g < groups; g += NSP) {
+            const uint2 w = field_near(c.rec, g);
+            const int i0 = w.x & 0xFFFF, left = c.count - 4 * g;
+            // (beyond the list's end: the group's first obstacle again, taken off below)
+            const int i1 = left > 1 ? w.x >> 16 : i0, i2 = left > 2 ? w.y & 0xFFFF : i0, i3 = left > 3 ? w.y >> 16 : i0;
+            if (__ballot(left < 4) == 0) {
+                half += body.four(L.obs[i0], L.obs[i1], L.obs[i2], L.obs[i3]);
+            } else {
+                const float f0 = body.one(L.obs[i0]), f1 = body.one(L.obs[i1]);
+                const float f2 = body.one(L.obs[i2]), f3 = body.one(L.obs[i3]);
+                half += (f0 + (left > 1 ? f1 : 0.0f)) + ((left > 2 ? f2 : 0.0f) + (left > 3 ? f3 : 0.0f));
+            }
+        }
+        near = 2.0f * half;
+    } else {
+        for (int k = sp; k < c.count; k += NSP) {
+            const uint2 w = field_near(c.rec, k >> 2);
+            const uint32_t word = (k & 2) ? w.y : w.x;
+            const float4 o = L.obs[(k & 1) ? word >> 16 : word & 0xFFFF];
+            const float ex = pose.x - o.x, ey = pose.y - o.y;
+            const float ee = fmaf(ex, ex, fmaf(ey, ey, o.w));
+            const float pu = fmaf(ex, pose.z, ey * pose.w);
+#pragma unroll 1
+            for (int i = 0; i < 7; ++i) {
+                const float a = L.shape[i].x;
+                near += barrier_rcp(fminf(ee + fmaf(2.0f * a, pu, a * a), kHMax), p.h_eps);
+            }
+        }
+    }
+    return near + far;
+}
+
+// The same for any body, a point at a time: lane sp of 2^lg takes points sp,
+// sp + 2^lg, ...; each has its own cell.  IND: the smallest h over the near
+// obstacles instead (a far one is never below 0).
+template <bool IND>
+__device__ __forceinline__ float field_barrier_points(const DevParams& p, const TileLds& L, const float* cells, int P,
+                                                      float4 pose, int sp, int lg, bool& ok)
+{
+    float near = IND ? INFINITY : 0.0f, far = 0.0f;
+    ok = true;
+    for (int i = sp; i < P; i += 1 << lg) {
+        const float2 ab = L.shape[i];
+        const float a = ab.x, b = ab.y;
+        const float dx = fmaf(a, pose.z, -b * pose.w), dy = fmaf(a, pose.w, b * pose.z);
+        const FieldCell c = field_cell(L, cells, pose.x + dx, pose.y + dy);
+        ok = ok && c.ok;
+        if constexpr (!IND) {
+            const float u[1] = {c.u}, v[1] = {c.v};
+            far += field_far<1>(c.rec, u, v);
+        }
+        for (int g = 0; 4 * g < c.count; ++g) {
+            const uint2 w = field_near(c.rec, g);
+            const int left = c.count - 4 * g, i0 = w.x & 0xFFFF;
+            const int id[4] = {i0, left > 1 ? (int)(w.x >> 16) : i0, left > 2 ? (int)(w.y & 0xFFFF) : i0,
+                               left > 3 ? (int)(w.y >> 16) : i0};
+            float h[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 o = L.obs[id[k]];
+                const float ex = (pose.x - o.x) + dx, ey = (pose.y - o.y) + dy;
+                h[k] = fmaf(ex, ex, fmaf(ey, ey, o.w));
+            }
+            if constexpr (IND) {
+                near = fminf(near, fminf(fminf(h[0], h[1]), fminf(h[2], h[3])));
+            } else {
+                // 1/h of an obstacle beyond the list's end: 1/kHMax (1e-9 of a term)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) h[k] = k < left ? clamp_h(h[k], p.h_eps) : kHMax;
+                near += reciprocal_total<4>(h);
+            }
+        }
+    }
+    return IND ? near : near + far;
 }
 
 // The costmap terms of one pose (every shape point): sum_i B(sdf(p_i)), or
@@ -770,40 +1060,6 @@ __device__ __forceinline__ float map_terms(const DevParams& p, int P, float4 pos
     return acc;
 }
 
-// The comparison controllers' constraint test of one pose (Sec. IV-A's
-// weighted indicator): lane sp of a group of js = 2^lg lanes returns the
-// smallest h of every shape point against obstacles sp, sp + js, ... (+inf
-// when it has none); with the costmap's smallest value (map_terms), the
-// group's minimum decides whether the pose violates a constraint (h < 0).
-// General form h = (|e|^2 - r^2) + 2 e.d_i + |d_i|^2, as the runtime-P
-// barrier takes it.
-__device__ __forceinline__ float clearance_pose(const DevParams& p, const TileLds& L, int P, const float* sa2,
-                                                const float* sb2, const float* ss, float4 pose, int sp, int lg)
-{
-    constexpr int PM = MPPI_PMAX;
-    const float cs = pose.z, sn = pose.w;
-    const int J = p.J, js = 1 << lg;
-    float lo = INFINITY, lo2 = INFINITY;
-    float tx[PM], ty[PM];       // 2 d_i
-#pragma unroll
-    for (int i = 0; i < PM; ++i) {
-        tx[i] = fmaf(sa2[i], cs, -sb2[i] * sn);
-        ty[i] = fmaf(sa2[i], sn, sb2[i] * cs);
-    }
-    for (int j = sp; j < J; j += js) {
-        const float4 o = L.obs[j];
-        const float ex = pose.x - o.x, ey = pose.y - o.y;
-        const float ee = fmaf(ex, ex, fmaf(ey, ey, o.z));
-#pragma unroll
-        for (int i = 0; i < PM; i += 2) {
-            if (i < P) lo = fminf(lo, fmaf(ex, tx[i], fmaf(ey, ty[i], ee + ss[i])));
-            if (i + 1 < P) lo2 = fminf(lo2, fmaf(ex, tx[i + 1], fmaf(ey, ty[i + 1], ee + ss[i + 1])));
-        }
-    }
-    lo = fminf(lo, lo2);
-    return lo;
-}
-
 // ---------------------------------------------------------------------------
 // One tile of S samples: rollout and the tile's softmax partials.
 // PT = compile-time number of shape points (0: runtime P <= MPPI_PMAX; the
@@ -832,18 +1088,22 @@ __device__ __forceinline__ float clearance_pose(const DevParams& p, const TileLd
 // contiguous run of obstacles at a time; the nsp partial sums meet by wave
 // shuffles.
 // ---------------------------------------------------------------------------
-template <int MODEL, int S, int PT, bool IND, bool MAP>
+template <int MODEL, int S, int PT, bool IND, bool MAP, bool FIELD>
 __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, unsigned char* smem)
 {
     static_assert(!IND || PT == 0, "the indicator runs on the runtime-P tile");
+    static_assert(!FIELD || PT != 8, "the vehicle's field takes the body a point at a time");
     constexpr int NS = Model<MODEL>::NS;
-    constexpr int PM = PT ? PT : MPPI_PMAX;
     constexpr int DW = (S + kWave - 1) / kWave;     // waves that own samples
     constexpr int POOL0 = DW * kWave;               // first thread of the other waves
     static_assert(S >= 16 && S <= kMaxTile && (S & (S - 1)) == 0, "tile size");
     static_assert(POOL0 % S == 0 || S > POOL0, "a thread's items belong to one sample");
+    constexpr int RS = S + kRowPad;                 // slots from one step to the next
+    auto slot = [](int item) __attribute__((always_inline)) { return item + item / S; };   // of item (step, sample)
+    static_assert(kRowPad == 1, "slot()");
     static_assert(2 * S <= kRollBlock && (kRollBlock - POOL0) % S == 0, "tile size");
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int J = p.J, T = p.T, K = p.K, Kp = p.Kp;
     const int P = PT ? PT : p.P;
     const int tc = tile_chunk(J, T, NS, S);
@@ -910,13 +1170,35 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         const float v = i == tid ? ref0 : p.xref[i];
         L.ref[i] = a == 0 ? (float)((double)v - ox) : a == 1 ? (float)((double)v - oy) : v;
     }
+    if (FIELD && tid < P) L.shape[tid] = make_float2(p.shape[tid][0], p.shape[tid][1]);
+    // the far field's grids from the start position
+    if (FIELD && tid < kFieldLevels) {
+        const FieldLevel lv = p.field->level[tid];
+        FieldGrid g{};
+        if (p.field->valid) {
+            const double gx = (ox - lv.x0) / lv.side, gy = (oy - lv.y0) / lv.side;
+            const double cx = fmin(fmax(floor(gx), -1e9), 1e9), cy = fmin(fmax(floor(gy), -1e9), 1e9);
+            const float W = (float)(0.5 * lv.side) + p.field->margin;
+            g.ix = (int32_t)cx;
+            g.iy = (int32_t)cy;
+            g.nx = lv.nx;
+            g.ny = lv.ny;
+            g.base = lv.base;
+            g.fx = (float)(gx - cx);
+            g.fy = (float)(gy - cy);
+            g.inv = (float)(1.0 / lv.side);
+            g.half = (float)(lv.side / (double)W);
+            g.iw = 1.0f / W;
+        }
+        L.grid[tid] = g;
+    }
     float inv_res = 0.0f, offx = 0.0f, offy = 0.0f;
     // MAP: the controller has a costmap (p.sdf set); the tiles without one
     // carry none of its code
     if constexpr (MAP) {
-        inv_res = (float)(1.0 / (double)p.map_res);
-        offx = (float)((ox - (double)p.map_x0) / (double)p.map_res - 0.5);
-        offy = (float)((oy - (double)p.map_y0) / (double)p.map_res - 0.5);
+        inv_res = uniform((float)(1.0 / (double)p.map_res));
+        offx = uniform((float)((ox - (double)p.map_x0) / (double)p.map_res - 0.5));
+        offy = uniform((float)((oy - (double)p.map_y0) / (double)p.map_res - 0.5));
     }
     lds_barrier();
     // the largest |o|^2 over the obstacles (non-negative floats order as
@@ -931,19 +1213,11 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     const bool valid = owner && k < K;
 
     const float sqS = sqrtf(S_e);
-    const float scale0 = sqS * p.sigma[0], scale1 = sqS * p.sigma[1];
+    const float scale0 = uniform(sqS * p.sigma[0]), scale1 = uniform(sqS * p.sigma[1]);
     const bool normal_law = p.sampling == MPPI_SAMPLE_NORMAL;
-    const float cw0 = p.sigma[0] > 0.0f ? p.gamma_u / (S_e * p.sigma[0] * p.sigma[0]) : 0.0f;
-    const float cw1 = p.sigma[1] > 0.0f ? p.gamma_u / (S_e * p.sigma[1] * p.sigma[1]) : 0.0f;
+    const float cw0 = uniform(p.sigma[0] > 0.0f ? p.gamma_u / (S_e * p.sigma[0] * p.sigma[0]) : 0.0f);
+    const float cw1 = uniform(p.sigma[1] > 0.0f ? p.gamma_u / (S_e * p.sigma[1] * p.sigma[1]) : 0.0f);
 
-    // the recurrences' state: heading and companion on lanes 0..S-1, position
-    // and velocity of axis tid / S on lanes 0..2S-1 (with the sine and cosine
-    // of the last heading)
-    float th = xs.v[2], hw = Model<MODEL>::W ? xs.v[Model<MODEL>::W] : 0.0f;
-    const int axis = tid / S;
-    float q = 0.0f, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
-    float sn_old, cs_old;
-    heading_sincos(xs.v[2], sn_old, cs_old);
     // eq. barrier_update is linear in beta, so beta_t = bv_t + c_t with the
     // sample-dependent part bv_t = b_t + gamma_B bv_{t-1} (bv_0 = beta_0) and
     // the common part c_t = gamma_B (c_{t-1} - beta_d) (c_0 = 0), whose sum is
@@ -951,18 +1225,25 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // The common part's cost R_B sum_t c_t is the same for every sample and is
     // added in FP64 (cshift), so a large beta_d cannot swamp the FP32 sums;
     // the host forms its factor R_B sum_t c_t / beta_d once per controller.
-    float beta = 0.0f, beta0 = 0.0f, beta_d = 0.0f;
     double cost = 0.0;          // this thread's share of the cost of sample s_mine
 
-    float sa2[PM], sb2[PM], ss[PM];       // 2 s_i and |s_i|^2
+    // 2 s_i and |s_i|^2 of the layout forms (uniform: kept in scalar registers)
+    constexpr int PM = PT ? PT : 1;
+    float sa2[PM], sb2[PM], ss[PM];
+    if constexpr (PT != 0) {
 #pragma unroll
-    for (int i = 0; i < PM; ++i) {
-        const float a = (PT || i < P) ? p.shape[i][0] : 0.0f;
-        const float b = (PT || i < P) ? p.shape[i][1] : 0.0f;
-        sa2[i] = 2.0f * a;
-        sb2[i] = 2.0f * b;
-        ss[i] = fmaf(a, a, b * b);
+        for (int i = 0; i < PM; ++i) {
+            const float a = p.shape[i][0], b = p.shape[i][1];
+            sa2[i] = uniform(2.0f * a);
+            sb2[i] = uniform(2.0f * b);
+            ss[i] = uniform(fmaf(a, a, b * b));
+        }
     }
+    // What a recurrence carries from one chunk to the next, in the space of
+    // the partial costs: heading and companion by chunk parity, barrier state.
+    float2* carry_h = reinterpret_cast<float2*>(L.red);     // [2][kMaxTile]
+    float* carry_b = reinterpret_cast<float*>(L.red) + 4 * kMaxTile;
+    static_assert(5 * kMaxTile * 4 <= kRollBlock * 8, "carry");
 
     // the noise of sample kk at step t (Sec. IV-C mixture, scaled per Alg. 1)
     auto noise_of = [&](uint4 r) __attribute__((always_inline)) {
@@ -970,8 +1251,17 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     };
     auto noise_at = [&](int kk, int t) __attribute__((always_inline)) { return noise_of(philox_at(kk, t)); };
 
+    // The thread's index as the phases of a chunk use it: opaque to the
+    // compiler, which otherwise forms every phase's addresses before the chunk
+    // loop and holds them through the barrier units (70 registers spilled).
+    auto phase_tid = [&]() __attribute__((always_inline)) {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+
     // the inputs and the control cost of item idx (step t) from its Philox words
-    auto input = [&](int idx, int t, uint4 words) __attribute__((always_inline)) {
+    auto input = [&](int idx, int t, int s, uint4 words) __attribute__((always_inline)) {
         const float2 z = noise_of(words);
         const float2 u = L.U[t];
         const float v0 = u.x + z.x, v1 = u.y + z.y;
@@ -979,18 +1269,19 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         const float s1 = fminf(fmaxf(v1, p.u_min[1]), p.u_max[1]);
         float f0, f1;
         Model<MODEL>::inputs(p, s0, s1, f0, f1);
-        L.a[idx] = make_float4(f0, f1, 0.0f, 0.0f);
-        cost += (double)(cw0 * u.x * v0 + cw1 * u.y * v1);
-        if (keep_noise) L.nz[t * S + s_mine] = z;
+        L.a[slot(idx)] = make_float4(f0, f1, 0.0f, 0.0f);
+        cost += (double)(cw0 * u.x) * (double)v0 + (double)(cw1 * u.y) * (double)v1;
+        if (keep_noise) L.nz[t * S + s] = z;
     };
 
     // phase 1: the inputs of the n steps from t0 on, over threads [first, block)
     auto inputs_phase = [&](int t0, int n, int first) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         int idx = tid - first;
         uint4 w = w0;
         if (t0 != 0 && idx < n * S) w = philox_at(tile * S + s_mine, t0 + idx / S);
         while (idx < n * S) {
-            input(idx, t0 + idx / S, w);
+            input(idx, t0 + idx / S, s_mine, w);
             idx += kRollBlock - first;
             if (idx < n * S) w = philox_at(tile * S + s_mine, t0 + idx / S);
         }
@@ -1010,22 +1301,45 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         for (; tt < n; ++tt) step(tt, load(tt));
     };
 
-    // phase 2 (owner lanes): theta into a.z, its companion into a.y
-    auto headings_phase = [&](int n) __attribute__((always_inline)) {
+    // phase 2 (owner lanes): theta into a.z, its companion into a.y; after the
+    // last step, their terminal cost
+    auto headings_phase = [&](int c, int n) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
+        constexpr int W = Model<MODEL>::W;
         float4* a = L.a + tid;
+        float th = xs.v[2], hw = W ? xs.v[W] : 0.0f;
+        if (c > 0) {
+            const float2 h = carry_h[((c - 1) & 1) * kMaxTile + tid];
+            th = h.x;
+            hw = h.y;
+        }
         walk(
-            n, [&](int tt) __attribute__((always_inline)) { return make_float2(a[tt * S].x, a[tt * S].y); },
+            n, [&](int tt) __attribute__((always_inline)) { return make_float2(a[tt * RS].x, a[tt * RS].y); },
             [&](int tt, float2 in) __attribute__((always_inline)) {
                 const float y = Model<MODEL>::heading(p.dt, th, hw, in.x, in.y);
-                a[tt * S] = make_float4(in.x, y, th, 0.0f);
+                a[tt * RS] = make_float4(in.x, y, th, 0.0f);
             });
+        if (c + 1 < nch) {
+            carry_h[(c & 1) * kMaxTile + tid] = make_float2(th, hw);
+        } else {
+            const float* rf = L.ref + T * NS;
+            const float d2 = th - rf[2];
+            float f = p.Qf[2] * (d2 * d2);
+            if constexpr (W != 0) {
+                const float dw = hw - rf[W];
+                f = fmaf(p.Qf[W], dw * dw, f);
+            }
+            cost += (double)f;
+        }
     };
 
     // phase 3: sines, cosines and the headings' tracking cost
     auto sines_phase = [&](int t0, int n) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         constexpr int W = Model<MODEL>::W;
         for (int idx = tid; idx < n * S; idx += kRollBlock) {
-            const float4 in = L.a[idx];
+            float4& at = L.a[slot(idx)];
+            const float4 in = at;
             float sn, cn;
             heading_sincos(in.z, sn, cn);
             const float* rf = L.ref + (t0 + idx / S + 1) * NS;
@@ -1036,34 +1350,60 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 c = fmaf(p.Q[W], dw * dw, c);
             }
             cost += (double)c;
-            L.a[idx] = make_float4(in.x, in.y, sn, cn);
+            at = make_float4(in.x, in.y, sn, cn);
         }
     };
 
-    // phase 4 (lanes 0..2S-1): positions and velocities
-    auto positions_phase = [&](int n) __attribute__((always_inline)) {
+    // phase 4 (lanes 0..2S-1): positions and velocities; after the last step,
+    // their terminal cost
+    auto positions_phase = [&](int c, int n) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
+        const int axis = tid / S;
         const float4* a = L.a + s_mine;
         float* pos = (axis == 0 ? L.px : L.py) + s_mine;
         [[maybe_unused]] float* vel = (axis == 0 ? L.vx : L.vy) + s_mine;
+        float q = 0.0f, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
+        float th = xs.v[2];
+        if (c > 0) {        // (this lane's own last step of the chunk before)
+            const float2 h = carry_h[((c - 1) & 1) * kMaxTile + s_mine];
+            th = h.x;
+            q = pos[(tc - 1) * RS];
+            if constexpr (NS > 4) v = vel[(tc - 1) * RS];
+            else v = h.y;
+        }
+        float sn, cs;       // of the heading before the step
+        heading_sincos(th, sn, cs);
         walk(
-            n, [&](int tt) __attribute__((always_inline)) { return a[tt * S]; },
+            n, [&](int tt) __attribute__((always_inline)) { return a[tt * RS]; },
             [&](int tt, float4 in) __attribute__((always_inline)) {
-                Model<MODEL>::position(p, axis, q, v, in.x, in.y, sn_old, cs_old);
-                sn_old = in.z;
-                cs_old = in.w;
-                pos[tt * S] = q;
-                if constexpr (NS > 4) vel[tt * S] = v;
+                Model<MODEL>::position(p, axis, q, v, in.x, in.y, sn, cs);
+                sn = in.z;
+                cs = in.w;
+                pos[tt * RS] = q;
+                if constexpr (NS > 4) vel[tt * RS] = v;
             });
+        if (c + 1 == nch) {
+            const float* rf = L.ref + T * NS;
+            const float d0 = q - rf[axis];
+            float f = p.Qf[axis] * (d0 * d0);
+            if constexpr (NS > 4) {
+                const float d3 = v - rf[3 + axis];
+                f = fmaf(p.Qf[3 + axis], d3 * d3, f);
+            }
+            cost += (double)f;
+        }
     };
 
     // phase 5, first part: the positions' (and velocities') tracking cost
     auto tracking_cost = [&](int t0, int n) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         for (int idx = tid; idx < n * S; idx += kRollBlock) {
             const float* rf = L.ref + (t0 + idx / S + 1) * NS;
-            const float d0 = L.px[idx] - rf[0], d1 = L.py[idx] - rf[1];
+            const int at = slot(idx);
+            const float d0 = L.px[at] - rf[0], d1 = L.py[at] - rf[1];
             float c = fmaf(p.Q[1], d1 * d1, p.Q[0] * (d0 * d0));
             if constexpr (NS > 4) {
-                const float d3 = L.vx[idx] - rf[3], d4 = L.vy[idx] - rf[4];
+                const float d3 = L.vx[at] - rf[3], d4 = L.vy[at] - rf[4];
                 c = fmaf(p.Q[3], d3 * d3, c);
                 c = fmaf(p.Q[4], d4 * d4, c);
             }
@@ -1086,16 +1426,41 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // obstacles) and leave the last ones alone on their SIMDs, waiting on
     // their own latencies.
     auto units_phase = [&](int c, int n) __attribute__((always_inline)) {
+        const int lane = phase_tid() & (kWave - 1);
         const int items = n * S;
-        const int lg = (lg_pack >> (c == nch - 1 ? 4 : 0)) & 15;
+        int lg = (lg_pack >> (c == nch - 1 ? 4 : 0)) & 15;
+        [[maybe_unused]] const float* cells = nullptr;
+        if constexpr (FIELD) {
+            // enough lanes per item to give every wave a unit
+            cells = reinterpret_cast<const float*>(p.field) + 64;
+            lg = 0;
+            while (lg < kFieldLgMax && items << lg <= (kRollWaves - 1) * kWave) ++lg;
+        }
         const int ounits = ((items << lg) + kWave - 1) / kWave;
         const int munits = MAP ? (items + kWave - 1) / kWave : 0;
         const int units = ounits + munits + ((!IND && c == 0) ? 1 : 0);
         [[maybe_unused]] float omax2 = 0.0f;
-        if constexpr (PT != 0) omax2 = 2.0f * __int_as_float(*L.omax);
-        auto pose_of = [&](int item) __attribute__((always_inline)) {
-            const float4 a = L.a[item];
-            return make_float4(L.px[item], L.py[item], a.w, a.z);
+        if constexpr (PT != 0) omax2 = uniform(2.0f * __int_as_float(*L.omax));
+        auto pose_of = [&](int at) __attribute__((always_inline)) {
+            const float4 a = L.a[at];
+            return make_float4(L.px[at], L.py[at], a.w, a.z);
+        };
+        // With the far field the items are taken sixteen steps of a sample at
+        // a time: such poses lie close, so neighbouring lanes read the same
+        // cells' lines (of the records and the costmap) and have like near
+        // lists, where lanes of one step read a line each.
+        auto in_order = [&](int o) __attribute__((always_inline)) {
+            if constexpr (FIELD) {
+                constexpr int kOrder = MODEL == MPPI_CAR ? 4 : 16;
+                const int blk = o / (kOrder * S), r = o - blk * (kOrder * S), left = n - blk * kOrder;
+                int t = r & (kOrder - 1), s = r / kOrder;
+                if (left < kOrder) {        // the last, shorter block (r < 4096: exact)
+                    s = (int)(((float)r + 0.5f) * __builtin_amdgcn_rcpf((float)left));
+                    t = r - s * left;
+                }
+                return (blk * kOrder + t) * RS + s;
+            }
+            return slot(o);
         };
         auto next_unit = [&]() __attribute__((always_inline)) {
             int u = 0;
@@ -1103,33 +1468,69 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
             return __builtin_amdgcn_readfirstlane(u);
         };
         for (int u = next_unit(); u < units; u = next_unit()) {
-            int lgu = lg, item = (u * kWave + lane) >> lg, end = items;
+            // lane `sp` of the item's 2^lg: neighbouring lanes (one run of
+            // obstacles in LDS), with the far field lanes 64 / 2^lg apart
+            int lgu = lg, item, sp, at;
+            if (FIELD && u < ounits) {
+                const int per = kWave >> lg;
+                item = u * per + (lane & (per - 1));
+                sp = lane >> (6 - lg);
+            } else {
+                item = (u * kWave + lane) >> lg;
+                sp = lane & ((1 << lg) - 1);
+            }
+            int end = items;
             if (u >= ounits) {
                 const bool ends = u == ounits + munits;
                 if constexpr (MAP) {
-                    const int it = ends ? items + lane : (u - ounits) * kWave + lane;
-                    if (it < (ends ? items + kXSlots : items))
-                        L.mp[it] = map_terms<PT, IND>(p, P, pose_of(it), inv_res, offx, offy);
+                    const int it = ends ? lane : (u - ounits) * kWave + lane;
+                    if (it < (ends ? kXSlots : items)) {
+                        const int ma = ends ? n * RS + it : in_order(it);
+                        L.mp[ma] = map_terms<PT, IND>(p, P, pose_of(ma), inv_res, offx, offy);
+                    }
                 }
                 if (!ends) continue;
                 lgu = 5;
-                item = items + (lane >> 5);
-                end = items + kXSlots;
-            }
-            const int nsp = 1 << lgu, sp = lane & (nsp - 1);
-            float part = IND ? INFINITY : 0.0f;
-            if constexpr (IND) {
-                if (item < end) part = clearance_pose(p, L, P, sa2, sb2, ss, pose_of(item), sp, lgu);
-                for (int m = 1; m < nsp; m <<= 1) part = fminf(part, __shfl_xor(part, m));
+                item = lane >> 5;
+                sp = lane & 31;
+                end = kXSlots;
+                at = n * RS + item;
             } else {
-                if (item < end) part = fused_barrier_pose<MODEL, PT>(p, L, P, sa2, sb2, ss, pose_of(item), sp, lgu, omax2);
-                for (int m = 1; m < nsp; m <<= 1) part += __shfl_xor(part, m);
+                at = in_order(item);
             }
-            if (sp == 0 && item < end) L.b[item] = part;
+            const int nsp = 1 << lgu;
+            float part = IND ? INFINITY : 0.0f;
+            if (item < end) {
+                const float4 pose = pose_of(at);
+                bool walk_all = true;
+                if constexpr (FIELD) {
+                    if (u < ounits) {
+                        bool ok;
+                        if constexpr (PT == 7) {
+                            if (lgu == 0) part = field_barrier_axis<0>(p, L, cells, sa2, ss, pose, sp, omax2, ok);
+                            else if (lgu == 1) part = field_barrier_axis<1>(p, L, cells, sa2, ss, pose, sp, omax2, ok);
+                            else part = field_barrier_axis<2>(p, L, cells, sa2, ss, pose, sp, omax2, ok);
+                        } else {
+                            part = field_barrier_points<IND>(p, L, cells, P, pose, sp, lgu, ok);
+                        }
+                        walk_all = __ballot(!ok) != 0;
+                    }
+                }
+                if (walk_all) {
+                    if constexpr (PT == 0 || FIELD) part = walk_points<IND>(p, L, P, pose, sp, lgu);
+                    else part = fused_barrier_pose<MODEL, PT>(p, L, sa2, sb2, ss, pose, sp, lgu, omax2);
+                }
+            }
+            const int step = FIELD && u < ounits ? kWave >> lgu : 1;
+            for (int m = step; m < step * nsp; m <<= 1) {
+                const float other = __shfl_xor(part, m);
+                part = IND ? fminf(part, other) : part + other;
+            }
+            if (sp == 0 && item < end) L.b[at] = part;
         }
     };
 
-    // the fused barrier of item idx with its costmap part
+    // the fused barrier of slot idx with its costmap part
     auto barrier_at = [&](int idx) __attribute__((always_inline)) {
         float b = L.b[idx];
         if constexpr (MAP) b = IND ? fminf(b, L.mp[idx]) : b + L.mp[idx];
@@ -1137,28 +1538,27 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     };
     // barrier-state recursion over chunk c (owner lanes), in place
     auto beta_phase = [&](int c, int n) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         if constexpr (!IND) {
-            if (c == 0) {
-                beta0 = barrier_at(n * S);
-                beta_d = barrier_at(n * S + 1);
-                beta = beta0;
-            }
+            float beta = c == 0 ? barrier_at(n * RS) : carry_b[tid];      // (from beta_0)
             walk(
-                n, [&](int tt) __attribute__((always_inline)) { return barrier_at(tt * S + tid); },
+                n, [&](int tt) __attribute__((always_inline)) { return barrier_at(tt * RS + tid); },
                 [&](int tt, float b) __attribute__((always_inline)) {
                     beta = fmaf(p.gamma_b, beta, b);
-                    L.b[tt * S + tid] = beta;
+                    L.b[tt * RS + tid] = beta;
                 });
+            if (c + 1 < nch) carry_b[tid] = beta;
         }
     };
     // R_B beta of every item (with the indicator, the weight of every step
     // that violates a constraint), over threads [first, block)
     auto beta_cost = [&](int n, int first) __attribute__((always_inline)) {
+        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         for (int idx = tid - first; idx < n * S; idx += kRollBlock - first) {
             if constexpr (IND) {
-                if (barrier_at(idx) < 0.0f) cost += (double)p.collision_weight;
+                if (barrier_at(slot(idx)) < 0.0f) cost += (double)p.collision_weight;
             } else {
-                cost += (double)(p.r_b * L.b[idx]);
+                cost += (double)p.r_b * (double)L.b[slot(idx)];
             }
         }
     };
@@ -1175,7 +1575,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         lds_barrier();
         if (tid == kRollBlock - 1) L.next[(c + 1) & 1] = 0;
         if (wave < DW) {
-            if (owner) headings_phase(n);
+            if (owner) headings_phase(c, n);
         } else if (c > 0) {
             beta_cost(tc, POOL0);
         }
@@ -1188,12 +1588,12 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
             const float* xd = L.ref + T * NS;
             float sn, cn;
             heading_sincos(i == 0 ? xs.v[2] : xd[2], sn, cn);
-            L.a[n * S + i] = make_float4(0.0f, 0.0f, sn, cn);
-            L.px[n * S + i] = i == 0 ? 0.0f : xd[0];
-            L.py[n * S + i] = i == 0 ? 0.0f : xd[1];
+            L.a[n * RS + i] = make_float4(0.0f, 0.0f, sn, cn);
+            L.px[n * RS + i] = i == 0 ? 0.0f : xd[0];
+            L.py[n * RS + i] = i == 0 ? 0.0f : xd[1];
         }
         lds_barrier();
-        if (tid < 2 * S) positions_phase(n);
+        if (tid < 2 * S) positions_phase(c, n);
         lds_barrier();
         tracking_cost(t0, n);
         units_phase(c, n);
@@ -1205,35 +1605,15 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         if constexpr (!IND) lds_barrier();
         beta_cost(n, 0);
     }
-    // the terminal cost, from the lanes that hold the final state
-    {
-        const float* rf = L.ref + T * NS;
-        if (owner) {
-            constexpr int W = Model<MODEL>::W;
-            const float d2 = th - rf[2];
-            float c = p.Qf[2] * (d2 * d2);
-            if constexpr (W != 0) {
-                const float dw = hw - rf[W];
-                c = fmaf(p.Qf[W], dw * dw, c);
-            }
-            cost += (double)c;
-        }
-        if (tid < 2 * S) {
-            const float d0 = q - rf[axis];
-            float c = p.Qf[axis] * (d0 * d0);
-            if constexpr (NS > 4) {
-                const float d3 = v - rf[3 + axis];
-                c = fmaf(p.Qf[3 + axis], d3 * d3, c);
-            }
-            cost += (double)c;
-        }
-    }
     // the samples' costs: lanes of one sample within a wave, then the groups
     for (int m = S; m < kWave; m <<= 1) cost += __shfl_xor(cost, m);
     constexpr int RG = S < kWave ? kRollWaves : kRollBlock / S;
+    lds_barrier();          // (the carried state is spent)
     if (S >= kWave) L.red[tid] = cost;                       // [tid / S][tid % S]
     else if (lane < S) L.red[wave * S + lane] = cost;
     lds_barrier();
+    // (chunk 0's extra slots lie beyond every chunk's items)
+    const float beta0 = IND ? 0.0f : barrier_at(min(tc, T) * RS), beta_d = IND ? 0.0f : barrier_at(min(tc, T) * RS + 1);
     const double cshift = (double)beta_d * p.beta_d_weight;
     double total = 0.0;
     if (owner) {
@@ -1437,7 +1817,7 @@ __device__ __forceinline__ void touch_kernargs()
     asm volatile("" ::"s"(t));
 }
 
-template <int MODEL, int S, int PT, bool IND, bool MAP>
+template <int MODEL, int S, int PT, bool IND, bool MAP, bool FIELD>
 __global__ __launch_bounds__(kRollBlock) void k_rollout(DevParams p, StepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1453,14 +1833,14 @@ __global__ __launch_bounds__(kRollBlock) void k_rollout(DevParams p, StepArgs a)
         for (int i = 0; i < MPPI_NMAX + 2; ++i) xs.v[i] = a.x0[i];
     }
     xs.parity = a.parity;
-    rollout_tile<MODEL, S, PT, IND, MAP>(p, xcd_tile((int)blockIdx.x, p.tiles), xs, smem);
+    rollout_tile<MODEL, S, PT, IND, MAP, FIELD>(p, xcd_tile((int)blockIdx.x, p.tiles), xs, smem);
 }
 
 // Persistent rollout over a work list of (controller, tile) units of one
 // tile shape, taken in list order (the host sorts it longest-first): the
 // tile of the standalone kernel of that shape.  Every block leaves the loop
 // once the list is exhausted; the last block to leave resets the queue.
-template <int MODEL, int S, int PT, bool IND, bool MAP>
+template <int MODEL, int S, int PT, bool IND, bool MAP, bool FIELD>
 __global__ __launch_bounds__(kRollBlock) void k_batch_rollout(const DevParams* __restrict__ ps,
                                                               const BatchUnit* __restrict__ units, int nunits,
                                                               const BatchIn* __restrict__ in, uint32_t* queue)
@@ -1479,7 +1859,7 @@ __global__ __launch_bounds__(kRollBlock) void k_batch_rollout(const DevParams* _
 #pragma unroll
         for (int i = 0; i < MPPI_NMAX + 2; ++i) xs.v[i] = in[bu.ctrl].x0[i];
         xs.parity = in[bu.ctrl].parity;
-        rollout_tile<MODEL, S, PT, IND, MAP>(p, bu.tile, xs, smem);
+        rollout_tile<MODEL, S, PT, IND, MAP, FIELD>(p, bu.tile, xs, smem);
         __syncthreads();
     }
     if (threadIdx.x == 0) {
@@ -1491,66 +1871,60 @@ __global__ __launch_bounds__(kRollBlock) void k_batch_rollout(const DevParams* _
     }
 }
 
-// The batched kernel of one model's `key` (kind key / kTileSizes: layout
-// form, runtime P, indicator, each without and with a costmap; tile size
-// 16 << key % kTileSizes).
-template <int MODEL, int S>
-BatchRolloutKernel batch_kernel_of_kind(int kind)
+// The tile kinds of a model: layout form, runtime P, indicator, each without
+// and with a costmap, then the same six with the obstacles' far field.  (The
+// vehicle's field takes every body a point at a time: its layout form is its
+// runtime-P form there.)
+template <int MODEL, int S, template <int, int, int, bool, bool, bool> class K>
+auto kernel_of_kind(int kind)
 {
-    constexpr int PD = MODEL == MPPI_CAR ? 8 : 7;
+    constexpr int PD = MODEL == MPPI_CAR ? 8 : 7, PF = MODEL == MPPI_CAR ? 0 : 7;
     switch (kind) {
-    case 0: return k_batch_rollout<MODEL, S, PD, false, false>;
-    case 1: return k_batch_rollout<MODEL, S, PD, false, true>;
-    case 2: return k_batch_rollout<MODEL, S, 0, false, false>;
-    case 3: return k_batch_rollout<MODEL, S, 0, false, true>;
-    case 4: return k_batch_rollout<MODEL, S, 0, true, false>;
-    default: return k_batch_rollout<MODEL, S, 0, true, true>;
+    case 0: return K<MODEL, S, PD, false, false, false>::get();
+    case 1: return K<MODEL, S, PD, false, true, false>::get();
+    case 2: return K<MODEL, S, 0, false, false, false>::get();
+    case 3: return K<MODEL, S, 0, false, true, false>::get();
+    case 4: return K<MODEL, S, 0, true, false, false>::get();
+    case 5: return K<MODEL, S, 0, true, true, false>::get();
+    case 6: return K<MODEL, S, PF, false, false, true>::get();
+    case 7: return K<MODEL, S, PF, false, true, true>::get();
+    case 8: return K<MODEL, S, 0, false, false, true>::get();
+    case 9: return K<MODEL, S, 0, false, true, true>::get();
+    case 10: return K<MODEL, S, 0, true, false, true>::get();
+    default: return K<MODEL, S, 0, true, true, true>::get();
+    }
+}
+
+template <int MODEL, int S, int PT, bool IND, bool MAP, bool FIELD> struct StepKernel {
+    static auto get() { return &k_rollout<MODEL, S, PT, IND, MAP, FIELD>; }
+};
+template <int MODEL, int S, int PT, bool IND, bool MAP, bool FIELD> struct BatchKernel {
+    static auto get() { return &k_batch_rollout<MODEL, S, PT, IND, MAP, FIELD>; }
+};
+
+// The kernel of `key` (kind key / kTileSizes, tile size 16 << key % kTileSizes).
+template <int MODEL, template <int, int, int, bool, bool, bool> class K>
+auto kernel_of(int key)
+{
+    const int kind = key / kTileSizes;
+    switch (key % kTileSizes) {
+    case 0: return kernel_of_kind<MODEL, 16, K>(kind);
+    case 1: return kernel_of_kind<MODEL, 32, K>(kind);
+    case 2: return kernel_of_kind<MODEL, 64, K>(kind);
+    case 3: return kernel_of_kind<MODEL, 128, K>(kind);
+    default: return kernel_of_kind<MODEL, 256, K>(kind);
     }
 }
 
 template <int MODEL>
-BatchRolloutKernel batch_kernel_of(int key)
-{
-    const int kind = key / kTileSizes;
-    switch (key % kTileSizes) {
-    case 0: return batch_kernel_of_kind<MODEL, 16>(kind);
-    case 1: return batch_kernel_of_kind<MODEL, 32>(kind);
-    case 2: return batch_kernel_of_kind<MODEL, 64>(kind);
-    case 3: return batch_kernel_of_kind<MODEL, 128>(kind);
-    default: return batch_kernel_of_kind<MODEL, 256>(kind);
-    }
-}
-
-template <int MODEL, int S>
-hipError_t launch_rollout_ms(const DevParams& p, const StepArgs& a, size_t lds, hipStream_t s)
-{
-    constexpr int PD = MODEL == MPPI_CAR ? 8 : 7;
-    const dim3 g(p.tiles), b(kRollBlock);
-    const bool map = p.sdf != nullptr;
-    if (p.cost_mode == MPPI_COST_INDICATOR) {
-        if (map) hipLaunchKernelGGL((k_rollout<MODEL, S, 0, true, true>), g, b, lds, s, p, a);
-        else hipLaunchKernelGGL((k_rollout<MODEL, S, 0, true, false>), g, b, lds, s, p, a);
-    } else if (p.P == PD && p.shape_kind != kShapeGeneral) {
-        if (map) hipLaunchKernelGGL((k_rollout<MODEL, S, PD, false, true>), g, b, lds, s, p, a);
-        else hipLaunchKernelGGL((k_rollout<MODEL, S, PD, false, false>), g, b, lds, s, p, a);
-    } else {
-        if (map) hipLaunchKernelGGL((k_rollout<MODEL, S, 0, false, true>), g, b, lds, s, p, a);
-        else hipLaunchKernelGGL((k_rollout<MODEL, S, 0, false, false>), g, b, lds, s, p, a);
-    }
-    return hipGetLastError();
-}
+BatchRolloutKernel batch_kernel_of(int key) { return kernel_of<MODEL, BatchKernel>(key); }
 
 template <int MODEL>
 hipError_t launch_rollout_m(const DevParams& p, const StepArgs& a, size_t lds, hipStream_t s)
 {
-    switch (p.spt) {
-    case 16: return launch_rollout_ms<MODEL, 16>(p, a, lds, s);
-    case 32: return launch_rollout_ms<MODEL, 32>(p, a, lds, s);
-    case 64: return launch_rollout_ms<MODEL, 64>(p, a, lds, s);
-    case 128: return launch_rollout_ms<MODEL, 128>(p, a, lds, s);
-    case 256: return launch_rollout_ms<MODEL, 256>(p, a, lds, s);
-    default: return hipErrorInvalidValue;
-    }
+    const auto k = kernel_of<MODEL, StepKernel>(tile_key(p));
+    hipLaunchKernelGGL(k, dim3(p.tiles), dim3(kRollBlock), lds, s, p, a);
+    return hipGetLastError();
 }
 
 }  // namespace

@@ -72,6 +72,7 @@ struct DevParams {
     double beta_d_weight;    // R_B sum_{t=1..T} c_t / beta_d, the common barrier-state cost per unit of beta_d
     const float* sgf_coef;   // [T][2m+1] smoothing weights of step t over its window
     const float* obs;        // [J][3] cx, cy, r (world frame)
+    const struct FieldHeader* field;    // the obstacles' far field (mppi_field.hpp), or null
     const float* sdf;        // [map_h][map_w] or null
     const float4* sdf4;      // [map_h-1][map_w-1] four-texel records of sdf (null: read sdf itself)
     const float* xref;       // [T+1][n] world frame
@@ -127,9 +128,10 @@ constexpr int kModels = 3;          // MPPI_QUAD6, MPPI_QUAD5, MPPI_CAR
 // size and tile kind, each holding the one tile the standalone kernel of that
 // shape holds (a kernel holding many tiles has the registers of the largest
 // and spills).  Kinds: the layout form of the paper's bodies, the runtime-P
-// form and the indicator tile, each without and with a costmap.
+// form and the indicator tile, each without and with a costmap; and the same
+// with the obstacles' far field.
 constexpr int kTileSizes = 5;       // S = 16, 32, 64, 128, 256
-constexpr int kTileKinds = 6;
+constexpr int kTileKinds = 12;
 constexpr int kBatchKeys = kTileSizes * kTileKinds;
 constexpr int kBatchGroups = kModels * kBatchKeys;
 
@@ -199,6 +201,19 @@ inline int32_t shape_form(int model, int P, const float (*sh)[2])
     return kShapeMirroredAxis;
 }
 
+// The tile kernel of a controller: kind x kTileSizes + size (see above).
+inline int tile_key(const DevParams& p)
+{
+    int size = 0;
+    for (int k = 0; k < kTileSizes; ++k)
+        if (p.spt == (16 << k)) size = k;
+    int kind = p.sdf != nullptr ? 1 : 0;
+    if (p.cost_mode == MPPI_COST_INDICATOR) kind += 4;
+    else if (!(p.P == fixed_points(p.model) && p.shape_kind != kShapeGeneral)) kind += 2;
+    if (p.field) kind += 6;
+    return kind * kTileSizes + size;
+}
+
 inline int state_dim(int model) { return model == MPPI_QUAD6 ? 6 : model == MPPI_QUAD5 ? 5 : 4; }
 
 // LDS obstacle slots (at least one, so the carve-up never has a zero-size array).
@@ -258,6 +273,9 @@ constexpr size_t kNoiseLdsMax = 81920;  // most LDS the tile's kept noise may ta
 // the poses of x0 and x_d = x_ref[T] there, whose fused barriers are beta_0
 // and beta_d.
 constexpr int kXSlots = 2;
+// The slots of one step lie S + 1 apart, so that lanes walking one sample's
+// steps meet different LDS banks.
+constexpr int kRowPad = 1;
 
 // Bytes per (step, sample) slot: inputs/heading (float4), position, for the
 // quadrotors (n > 4) velocity, the fused barrier and the costmap's part.
@@ -274,7 +292,9 @@ __host__ __device__ inline size_t tile_fixed_lds(int J, int T, int n)
     b += (size_t)kMaxTile * 8;                  // tile exponentials
     b += (size_t)kRollBlock * 8;                // partial costs per thread group
     b += 16 * 8;                                // block-reduction slots
-    b += 64;                                    // the largest |o|^2
+    b += 64;                                    // the largest |o|^2, unit counters
+    b += 192;                                   // the far field's grids, seen from the start position
+    b += MPPI_PMAX * 8;                         // shape points
     return b;
 }
 
@@ -282,7 +302,7 @@ __host__ __device__ inline size_t tile_fixed_lds(int J, int T, int n)
 // the epilogue use it once it is spent).
 __host__ __device__ inline size_t slot_area(int T, int n, int S, int tc)
 {
-    const size_t b = ((size_t)tc * S + kXSlots) * slot_bytes(n);
+    const size_t b = ((size_t)tc * (S + kRowPad) + kXSlots) * slot_bytes(n);
     const size_t sgf = (size_t)T * 16;
     return ((b > sgf ? b : sgf) + 15) & ~(size_t)15;
 }
@@ -306,7 +326,7 @@ __host__ __device__ inline int tile_chunk(int J, int T, int n, int S)
     const size_t used = tile_fixed_lds(J, T, n) + (tile_keeps_noise(J, T, n, S) ? (size_t)T * S * 8 : 0);
     const size_t room = kTileLds > used + 16 ? kTileLds - used - 16 : 0;
     const long slots = (long)(room / slot_bytes(n)) - kXSlots;
-    const long fit = slots / S;
+    const long fit = slots / (S + kRowPad);
     if (fit >= T) return T;
     const int round = kRollBlock / S;
     if (fit >= round) return (int)(fit / round * round);

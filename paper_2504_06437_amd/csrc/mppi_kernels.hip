@@ -327,11 +327,454 @@ __global__ __launch_bounds__(256) void k_philox_words(DevParams p, uint64_t coun
 }
 }  // namespace
 
+// ---------------------------------------------------------------------------
+// The obstacles' far field (mppi_field.hpp).
+// ---------------------------------------------------------------------------
+namespace {
+
+// Interpolation at the Padua points of degree n = 8 (Caliari, De Marchi and
+// Vianello, "Bivariate polynomial interpolation on the square at new nodal
+// sets", 2005; the explicit formula of Bos et al., 2006): the 45 points
+// (cos(j pi/n), cos(k pi/(n+1))), j + k even, determine a polynomial of total
+// degree n, whose Chebyshev coefficients are weighted sums of the values.
+// fit[p][q]: what the value at point p adds to the monomial coefficient q;
+// coefficient q = (8-l)(9-l)/2 + 8-l-k belongs to u^k v^l (rows of falling
+// powers of v, each in falling powers of u: the order Horner's rule takes).
+struct Padua {
+    double x[kFieldCoefs], y[kFieldCoefs];
+    double fit[kFieldCoefs][kFieldCoefs];
+};
+
+constexpr double cosine(double a)       // Taylor series, 0 <= a <= pi
+{
+    double t = 1.0, s = 1.0;
+    for (int i = 1; i <= 16; ++i) {
+        t *= -a * a / (double)((2 * i - 1) * (2 * i));
+        s += t;
+    }
+    return s;
+}
+
+constexpr Padua make_padua()
+{
+    constexpr int n = kFieldDeg;
+    constexpr double pi = 3.14159265358979323846;
+    Padua r{};
+    double mono[n + 1][n + 1] = {};     // T_i = sum_k mono[i][k] x^k
+    mono[0][0] = 1.0;
+    mono[1][1] = 1.0;
+    for (int i = 2; i <= n; ++i)
+        for (int k = 0; k <= i; ++k) mono[i][k] = (k > 0 ? 2.0 * mono[i - 1][k - 1] : 0.0) - mono[i - 2][k];
+    int p = 0;
+    for (int j = 0; j <= n; ++j)
+        for (int k = 0; k <= n + 1; ++k) {
+            if ((j + k) & 1) continue;
+            const double x = cosine(j * pi / n), y = cosine(k * pi / (n + 1));
+            const bool ex = j == 0 || j == n, ey = k == 0 || k == n + 1;
+            const double w = (ex && ey ? 0.5 : ex || ey ? 1.0 : 2.0) / (double)(n * (n + 1));
+            double tx[n + 1] = {1.0, x}, ty[n + 1] = {1.0, y};
+            for (int i = 2; i <= n; ++i) {
+                tx[i] = 2.0 * x * tx[i - 1] - tx[i - 2];
+                ty[i] = 2.0 * y * ty[i - 1] - ty[i - 2];
+            }
+            r.x[p] = x;
+            r.y[p] = y;
+            for (int a = 0; a <= n; ++a)
+                for (int b = 0; a + b <= n; ++b) {
+                    const double g = w * (a ? 2.0 : 1.0) * (b ? 2.0 : 1.0) * (a == n ? 0.5 : 1.0) * tx[a] * ty[b];
+                    for (int kk = a & 1; kk <= a; kk += 2)
+                        for (int l = b & 1; l <= b; l += 2)
+                            r.fit[p][(n - l) * (n - l + 1) / 2 + n - l - kk] += g * mono[a][kk] * mono[b][l];
+                }
+            ++p;
+        }
+    return r;
+}
+
+__device__ const Padua kPadua = make_padua();
+
+// A polynomial at (u, v), FP64: rows of falling powers of v, nine slots a row
+// in falling powers of u (the unused ones in front, zero).
+constexpr int kFieldRow = kFieldDeg + 1;
+
+__device__ __forceinline__ double field_eval_d(const double* c, double u, double v)
+{
+    double acc = 0.0;
+#pragma unroll 1
+    for (int i = 0; i < kFieldRow; ++i, c += kFieldRow) {
+        double r = c[0];
+#pragma unroll
+        for (int k = 1; k < kFieldRow; ++k) r = fma(r, u, c[k]);
+        acc = fma(acc, v, r);
+    }
+    return acc;
+}
+
+constexpr int kFieldBlock = 512;
+constexpr int kFieldWaves = kFieldBlock / kWave;
+// The thresholds a cell tries, and the one it takes when none holds.
+constexpr int kKappas = 3;
+__device__ constexpr float kKappa[kKappas + 1] = {3.25f, 4.0f, 4.75f, 6.0f};
+constexpr float kFieldTol = 1.5e-7f;        // of the macro cell's and of the cell's far sums, each
+
+// The relative error that an obstacle kappa half-widths off leaves.
+__device__ __forceinline__ float field_error(float kappa) { return 8.0f * exp2f(-9.25f * log2f(kappa + 1.0f)); }
+
+// Grid l of an obstacle set from its bounding box.
+__device__ FieldLevel field_level(int l, double cx, double cy, double w, double hh, int J, float margin)
+{
+    // cells of 0.3 obstacle spacings: about five obstacles near a cell, and
+    // no finer than the body they carry; twice and four times that outside
+    const double want = fmax(0.3 * sqrt(w * hh / J), (double)margin);
+    const int cap = l == 0 ? kFieldMacros0 : l == 1 ? kFieldMacros1 : kFieldMacros2;
+    const int base = l == 0 ? 0 : l == 1 ? kFieldMacros0 : kFieldMacros0 + kFieldMacros1;
+    // the box itself, and half and one and a half boxes around it
+    const double pad = l == 0 ? want : (l == 1 ? 0.5 : 1.5) * fmax(w, hh);
+    const double W = w + 2.0 * pad, H = hh + 2.0 * pad;
+    double c = fmax(sqrt(W * H / (cap * kMacro * kMacro)), want * (1 << l));
+    int mx = 1, my = 1;
+    for (int i = 0; i < 200; ++i) {
+        const double qx = ceil(W / (kMacro * c)), qy = ceil(H / (kMacro * c));
+        if (qx * qy <= (double)cap) {
+            mx = (int)qx;
+            my = (int)qy;
+            break;
+        }
+        c *= 1.04;
+    }
+    return FieldLevel{cx - 0.5 * mx * kMacro * c, cy - 0.5 * my * kMacro * c, c, mx * kMacro, my * kMacro,
+                      base * kMacro * kMacro, 0};
+}
+
+// Terms of an obstacle at (x, y) from a cell's centre, for the choice of
+// kappa: its edge's distance beyond the cell in half-widths, and its term at
+// the centre.
+__device__ __forceinline__ float field_kappa(float x, float y, float r, float W, float& f)
+{
+    const float dx = fmaxf(fabsf(x) - W, 0.0f), dy = fmaxf(fabsf(y) - W, 0.0f);
+    f = __builtin_amdgcn_rcpf(fmaf(x, x, fmaf(y, y, -r * r)));
+    return (sqrtf(fmaf(dx, dx, dy * dy)) - r) * __builtin_amdgcn_rcpf(W);
+}
+
+// One workgroup per macro cell of 4 x 4 cells.  The obstacles far from the
+// macro cell (at its own, four times larger, scale) enter one polynomial of
+// it, which each of its cells takes over by its values at the cell's nodes, so
+// a cell itself sums only the obstacles around its macro cell: about 40 of 400
+// where every cell summing them all took eight times the work.
+__global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restrict__ obs, int J, float margin, FieldHeader* hdr,
+                                                       float* __restrict__ cells)
+{
+    // per obstacle: the macro-far ones, macro-centred (near ones: at infinity),
+    // then in their place the macro-near ones (with r); the obstacles; the
+    // macro-near list
+    extern __shared__ __align__(16) unsigned char dyn[];
+    float4* so = reinterpret_cast<float4*>(dyn);
+    float4* sn = so;
+    float3* sobs = reinterpret_cast<float3*>(dyn + (size_t)J * 16);
+    uint16_t* snear = reinterpret_cast<uint16_t*>(dyn + (size_t)J * 28);
+    __shared__ double sfit[kFieldCoefs * kFieldCoefs];
+    __shared__ double sf[kFieldWaves][kFieldCoefs];     // node values
+    __shared__ double sc[kFieldRow * kFieldRow];        // the macro cell's polynomial, in rows
+    __shared__ float sred[kFieldWaves][8];
+    __shared__ FieldHeader sh;
+    __shared__ int snn;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    auto wave_fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // (the fit from LDS: read from memory where it is used, each of a cell's
+    // 45 terms waited on it)
+    for (int i = tid; i < kFieldCoefs * kFieldCoefs; i += kFieldBlock) sfit[i] = (&kPadua.fit[0][0])[i];
+    const bool node = lane < kFieldCoefs;
+    const int nq = node ? lane : 0;
+    const double nx = kPadua.x[nq], ny = kPadua.y[nq];
+    // the coefficient of lane q from the node values f
+    auto coefficient = [&](const double* f) {
+        double c = 0.0;
+#pragma unroll 9
+        for (int p = 0; p < kFieldCoefs; ++p) c = fma(sfit[p * kFieldCoefs + nq], f[p], c);
+        return c;
+    };
+    // ---- the grids (every workgroup forms them alike) ----
+    float b[4] = {INFINITY, INFINITY, INFINITY, INFINITY};      // min x, -max x, min y, -max y
+    bool bad = false;
+    for (int j = tid; j < J; j += kFieldBlock) {
+        const float x = obs[3 * j], y = obs[3 * j + 1], r = obs[3 * j + 2];
+        sobs[j] = make_float3(x, y, r);
+        bad |= !(fabsf(x) < 1e8f && fabsf(y) < 1e8f && fabsf(r) < 1e8f);
+        b[0] = fminf(b[0], x);
+        b[1] = fminf(b[1], -x);
+        b[2] = fminf(b[2], y);
+        b[3] = fminf(b[3], -y);
+    }
+    const bool wave_bad = __ballot(bad) != 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        for (int m = 32; m >= 1; m >>= 1) b[i] = fminf(b[i], __shfl_xor(b[i], m));
+        if (lane == 0) sred[wave][i] = b[i];
+    }
+    if (lane == 0) sred[wave][4] = wave_bad ? 1.0f : 0.0f;
+    __syncthreads();
+    if (tid < kFieldLevels) {
+        bool any = false;
+        for (int w = 0; w < kFieldWaves; ++w) {
+            for (int i = 0; i < 4; ++i) b[i] = fminf(b[i], sred[w][i]);
+            any |= sred[w][4] != 0.0f;
+        }
+        const double w = fmax(-(double)b[1] - b[0], 1.0), hh = fmax(-(double)b[3] - b[2], 1.0);
+        const bool valid = !any && fmax(w, hh) < 1e6;
+        const double cx = valid ? 0.5 * ((double)b[0] - b[1]) : 0.0, cy = valid ? 0.5 * ((double)b[2] - b[3]) : 0.0;
+        sh.level[tid] = field_level(tid, cx, cy, valid ? w : 1.0, valid ? hh : 1.0, J, margin);
+        if (tid == 0) {
+            sh.margin = margin;
+            sh.valid = valid;
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) *hdr = sh;
+    if (!sh.valid) return;
+    int l = 0, mi = blockIdx.x;
+    if (mi >= kFieldMacros0) { mi -= kFieldMacros0; l = 1; }
+    if (l == 1 && mi >= kFieldMacros1) { mi -= kFieldMacros1; l = 2; }
+    const FieldLevel lv = sh.level[l];
+    const int mxn = lv.nx / kMacro, myn = lv.ny / kMacro;
+    if (mi >= mxn * myn) return;
+    const int mx = mi % mxn, my = mi / mxn;
+    const double mside = kMacro * lv.side;
+    const double mcx = lv.x0 + (mx + 0.5) * mside, mcy = lv.y0 + (my + 0.5) * mside;
+    if (l > 0) {
+        // inside the finer grid no query comes here
+        const FieldLevel f = sh.level[l - 1];
+        const double e = 0.5 * mside + f.side;
+        if (mcx - e > f.x0 && mcx + e < f.x0 + f.nx * f.side && mcy - e > f.y0 && mcy + e < f.y0 + f.ny * f.side) return;
+    }
+    const float MW = (float)(0.5 * mside) + margin;
+    // the smallest kappa at which the far obstacles' errors stay below the
+    // tolerance, from the sums over the thresholds and the far sum
+    auto choose = [&](const float* err, const float* far) {
+        float k = kKappa[kKappas];
+        for (int i = kKappas - 1; i >= 0; --i)
+            if (err[i] <= kFieldTol * far[i]) k = kKappa[i];
+        return k;
+    };
+    auto add_errors = [&](float k, float f, float (&err)[kKappas], float (&far)[kKappas]) {
+        const float fe = f * field_error(k);
+#pragma unroll
+        for (int i = 0; i < kKappas; ++i) {
+            err[i] += k >= kKappa[i] ? fe : 0.0f;
+            far[i] += k >= kKappa[i] ? f : 0.0f;
+        }
+    };
+    // ---- macro cell: choose kappa, split the obstacles ----
+    float err[kKappas] = {}, far[kKappas] = {};
+    for (int j = tid; j < J; j += kFieldBlock) {
+        const float3 o = sobs[j];
+        const float x = (float)((double)o.x - mcx), y = (float)((double)o.y - mcy);
+        float f;
+        const float k = field_kappa(x, y, o.z, MW, f);
+        add_errors(k, f, err, far);
+    }
+    __shared__ float skap[kFieldWaves][2 * kKappas];
+#pragma unroll
+    for (int i = 0; i < kKappas; ++i) {
+        err[i] = wave_sum_f(err[i]);
+        far[i] = wave_sum_f(far[i]);
+        if (lane == 0) {
+            skap[wave][i] = err[i];
+            skap[wave][kKappas + i] = far[i];
+        }
+    }
+    __syncthreads();
+    for (int i = 0; i < kKappas; ++i) {
+        err[i] = far[i] = 0.0f;
+        for (int w = 0; w < kFieldWaves; ++w) {
+            err[i] += skap[w][i];
+            far[i] += skap[w][kKappas + i];
+        }
+    }
+    const float mk = choose(err, far);
+    const float4 away = make_float4(1e18f, 0.0f, 0.0f, 0.0f);       // 1/h = 1e-36
+    for (int j = tid; j < J; j += kFieldBlock) {
+        const float3 o = sobs[j];
+        const float x = (float)((double)o.x - mcx), y = (float)((double)o.y - mcy), r = o.z;
+        float f;
+        so[j] = field_kappa(x, y, r, MW, f) >= mk ? make_float4(x, y, -r * r, 0.0f) : away;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        int n = 0;
+        for (int j0 = 0; j0 < J; j0 += kWave) {
+            const int j = j0 + lane;
+            const bool near = j < J && so[j].x == 1e18f;
+            const uint64_t m = __ballot(near);
+            if (near) snear[n + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)j;
+            n += __popcll(m);
+        }
+        if (lane == 0) snn = n;
+    }
+    // ---- macro polynomial: a node per lane, the obstacles shared out to the waves ----
+    // the sum of 1/h over n obstacles at (x, y): FP32 terms, added up in FP64
+    // by eights
+    auto node_sum = [&](const float4* o, int n, float x, float y) {
+        double s = 0.0;
+        int j = 0;
+        for (; j + 8 <= n; j += 8) {
+            float a = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 c = o[j + i];
+                const float ex = x - c.x, ey = y - c.y;
+                a += __builtin_amdgcn_rcpf(fmaf(ex, ex, fmaf(ey, ey, c.z)));
+            }
+            s += (double)a;
+        }
+        for (; j < n; ++j) {
+            const float4 c = o[j];
+            const float ex = x - c.x, ey = y - c.y;
+            s += (double)__builtin_amdgcn_rcpf(fmaf(ex, ex, fmaf(ey, ey, c.z)));
+        }
+        return s;
+    };
+    {
+        const int q = (J + kFieldWaves - 1) / kFieldWaves, j0 = min(wave * q, J);
+        const double s = node_sum(so + j0, min(q, J - j0), (float)nx * MW, (float)ny * MW);
+        if (node) sf[wave][lane] = s;
+    }
+    __syncthreads();
+    if (tid < kFieldCoefs) {
+        double v = sf[0][tid];
+        for (int w = 1; w < kFieldWaves; ++w) v += sf[w][tid];
+        sf[0][tid] = v;
+    }
+    if (wave == 0) {
+        wave_fence();
+        // coefficient q of row i lies (i+1)(i+2)/2 - 1 - q before the row's end
+        int i = 0;
+        while ((i + 1) * (i + 2) / 2 <= nq) ++i;
+        for (int k = lane; k < kFieldRow * kFieldRow; k += kWave) sc[k] = 0.0;
+        wave_fence();
+        if (node) sc[i * kFieldRow + kFieldDeg + nq - ((i + 1) * (i + 2) / 2 - 1)] = coefficient(sf[0]);
+    }
+    const int nn = snn;
+    for (int i = tid; i < nn; i += kFieldBlock) {
+        const float3 o = sobs[snear[i]];
+        sn[i] = make_float4((float)((double)o.x - mcx), (float)((double)o.y - mcy), -o.z * o.z, o.z);
+    }
+    __syncthreads();
+    // ---- the macro cell's 16 cells, two per wave at once (one LDS read of an
+    // obstacle serves both: the reads bound the sums) ----
+    constexpr int C = kMacro * kMacro / kFieldWaves;
+    const float W = (float)(0.5 * lv.side) + margin, iMW = 1.0f / MW;
+    float cx[C], cy[C], ck[C];          // centres from the macro cell's; the chosen kappas
+    double v[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int ci = wave * C + c;
+        cx[c] = (float)((ci % kMacro - 0.5 * (kMacro - 1)) * lv.side);
+        cy[c] = (float)((ci / kMacro - 0.5 * (kMacro - 1)) * lv.side);
+        v[c] = field_eval_d(sc, (double)(fmaf((float)nx, W, cx[c]) * iMW), (double)(fmaf((float)ny, W, cy[c]) * iMW));
+        ck[c] = kKappa[kKappas];
+    }
+    // (around a large set the outer grids' cells take the widest kappa: the
+    // choice would cost as much as the sum)
+    if (nn <= 4 * kWave) {
+        float e[C][kKappas] = {}, fr[C][kKappas] = {};
+        for (int i0 = lane; i0 < nn; i0 += kWave) {
+            const float4 o = sn[i0];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                float f;
+                const float k = field_kappa(o.x - cx[c], o.y - cy[c], o.w, W, f);
+                add_errors(k, f, e[c], fr[c]);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            // (the macro-far part: its value at the first node will do)
+            const float macro = fmaxf(__shfl((float)v[c], 0), 0.0f);
+#pragma unroll
+            for (int i = 0; i < kKappas; ++i) {
+                e[c][i] = wave_sum_f(e[c][i]);
+                fr[c][i] = wave_sum_f(fr[c][i]) + macro;
+            }
+            ck[c] = choose(e[c], fr[c]);
+        }
+    }
+    float px[C], py[C];                 // this lane's node of either cell
+    int cnt[C];
+    float* rec[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int ci = wave * C + c, ix = mx * kMacro + ci % kMacro, iy = my * kMacro + ci / kMacro;
+        rec[c] = cells + (size_t)(lv.base + iy * lv.nx + ix) * kFieldWords;
+        px[c] = fmaf((float)nx, W, cx[c]);
+        py[c] = fmaf((float)ny, W, cy[c]);
+        cnt[c] = 0;
+    }
+    for (int i0 = 0; i0 < nn; i0 += kWave) {
+        const int n = min(kWave, nn - i0);
+        uint64_t far_of[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            bool near = false;
+            if (lane < n) {
+                const float4 o = sn[i0 + lane];
+                float f;
+                near = !(field_kappa(o.x - cx[c], o.y - cy[c], o.w, W, f) >= ck[c]);
+            }
+            const uint64_t m = __ballot(near);
+            const int at = cnt[c] + __popcll(m & ((1ull << lane) - 1ull));
+            if (near && at < kFieldNear) reinterpret_cast<uint16_t*>(rec[c] + kFieldCoefs + 1)[at] = snear[i0 + lane];
+            cnt[c] += __popcll(m);
+            far_of[c] = ~m;
+        }
+        // FP32 terms, added up in FP64 by eights
+        for (int j = 0; j < n; j += 8) {
+            float a[C] = {};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (j + i < n) {
+                    const float4 o = sn[i0 + j + i];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const float ex = px[c] - o.x, ey = py[c] - o.y;
+                        const float f = __builtin_amdgcn_rcpf(fmaf(ex, ex, fmaf(ey, ey, o.z)));
+                        a[c] += (far_of[c] >> (j + i)) & 1 ? f : 0.0f;
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[c] += (double)a[c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        if (node) sf[wave][lane] = v[c];
+        wave_fence();
+        if (node) rec[c][lane] = (float)coefficient(sf[wave]);
+        if (lane == 0) rec[c][kFieldCoefs] = __int_as_float(cnt[c] <= kFieldNear ? cnt[c] : kFieldFull);
+        wave_fence();
+    }
+}
+
+}  // namespace
+
+hipError_t launch_field(const float* d_obs, int J, float margin, void* d_field, hipStream_t s)
+{
+    if (J < 1 || J > MPPI_JMAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_field, dim3(kFieldMacros), dim3(kFieldBlock), ((size_t)J * 30 + 15) & ~(size_t)15, s, d_obs, J, margin,
+                       static_cast<FieldHeader*>(d_field), reinterpret_cast<float*>(static_cast<char*>(d_field) + 256));
+    return hipGetLastError();
+}
+
 bool tile_samples_supported(int S) { return S >= 16 && S <= kMaxTile && (S & (S - 1)) == 0; }
 
 hipError_t launch_rollout(const DevParams& p0, const StepArgs& a, hipStream_t s)
 {
     DevParams p = p0;
+    if (!tile_samples_supported(p.spt)) return hipErrorInvalidValue;
     p.lg_pack = tile_lg_pack(p.J, p.T, p.n, p.spt, p.P);
     const size_t lds = tile_lds_bytes(p.J, p.T, p.n, p.spt);
     switch (p.model) {
@@ -440,18 +883,7 @@ hipError_t launch_philox_words(const DevParams& p, uint64_t counter, uint32_t* d
     return hipGetLastError();
 }
 
-int batch_group(const DevParams& p)
-{
-    int size = 0;
-    for (int k = 0; k < kTileSizes; ++k)
-        if (p.spt == (16 << k)) size = k;
-    const int map = p.sdf != nullptr;
-    int kind;
-    if (p.cost_mode == MPPI_COST_INDICATOR) kind = 4 + map;
-    else if (p.P == fixed_points(p.model) && p.shape_kind != kShapeGeneral) kind = map;
-    else kind = 2 + map;
-    return p.model * kBatchKeys + kind * kTileSizes + size;
-}
+int batch_group(const DevParams& p) { return p.model * kBatchKeys + tile_key(p); }
 
 int batch_rollout_blocks_per_cu(int group, size_t lds)
 {

@@ -13,6 +13,7 @@
 #include <mutex>
 #include <string>
 
+#include "mppi_field.hpp"
 #include "mppi_internal.hpp"
 #include "mppi_runtime.hpp"
 
@@ -21,23 +22,29 @@ using namespace dbas;
 namespace {
 
 static __device__ __align__(256) unsigned char scratch[MPPI_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char field[kFieldBytes];      // the obstacles' far field
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
+void* g_field_ptr[kMaxDevices] = {};
 
-// The device address of this device's scratch array (the device is current).
-hipError_t scratch_address(int device, unsigned char** out)
+// The device addresses of this device's scratch and field arrays (the device
+// is current).
+hipError_t scratch_address(int device, unsigned char** out, void** out_field)
 {
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     if (!g_scratch_ptr[device]) {
-        void* ptr = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
+        void *ptr = nullptr, *fld = nullptr;
+        hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
+        if (e == hipSuccess) e = hipGetSymbolAddress(&fld, HIP_SYMBOL(field));
         if (e != hipSuccess) return e;
-        if (!ptr) return hipErrorInvalidSymbol;
+        if (!ptr || !fld) return hipErrorInvalidSymbol;
         g_scratch_ptr[device] = ptr;
+        g_field_ptr[device] = fld;
     }
     *out = static_cast<unsigned char*>(g_scratch_ptr[device]);
+    *out_field = g_field_ptr[device];
     return hipSuccess;
 }
 
@@ -120,7 +127,8 @@ extern "C" int mppi_step_noalloc(const mppi_config* cfg, const mppi_problem* pro
 
     hipError_t e = hipSetDevice(device);
     unsigned char* base = nullptr;
-    if (e == hipSuccess) e = scratch_address(device, &base);
+    void* field_mem = nullptr;
+    if (e == hipSuccess) e = scratch_address(device, &base, &field_mem);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(MPPI_E_DEVICE, std::string("scratch address: ") + hipGetErrorString(e));
@@ -153,6 +161,10 @@ extern "C" int mppi_step_noalloc(const mppi_config* cfg, const mppi_problem* pro
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_noalloc_init, dim3(1), dim3(64), 0, s, p.st, counter, S_e);
     e = hipGetLastError();
+    if (e == hipSuccess && field_wanted(p.model, p.K, p.T, p.J, p.P, p.shape_kind, p.cost_mode)) {
+        e = launch_field(p.obs, p.J, field_margin(p.model, p.P, p.shape_kind, p.cost_mode, p.shape), field_mem, s);
+        p.field = static_cast<const FieldHeader*>(field_mem);
+    }
     if (e == hipSuccess) e = launch_rollout(p, a, s);
     if (e == hipSuccess) e = launch_update(p, a, s);
     if (e != hipSuccess) {

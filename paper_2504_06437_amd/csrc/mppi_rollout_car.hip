@@ -1,5 +1,4 @@
-// Rollout kernels of the car model (the standalone tile kernels and the
-// batched persistent kernels), compiled in a unit of their own.
+// Standalone rollout kernels of the car model, compiled in a unit of their own.
 #include "mppi_device.hpp"
 
 namespace dbas {
@@ -8,7 +7,5 @@ hipError_t launch_rollout_car(const DevParams& p, const StepArgs& a, size_t lds,
 {
     return launch_rollout_m<MPPI_CAR>(p, a, lds, s);
 }
-
-BatchRolloutKernel batch_rollout_kernel_car(int key) { return batch_kernel_of<MPPI_CAR>(key); }
 
 }  // namespace dbas

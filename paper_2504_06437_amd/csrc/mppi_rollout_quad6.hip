@@ -1,5 +1,4 @@
-// Rollout kernels of the quad6 model (the standalone tile kernels and the
-// batched persistent kernels), compiled in a unit of their own.
+// Standalone rollout kernels of the quad6 model, compiled in a unit of their own.
 #include "mppi_device.hpp"
 
 namespace dbas {
@@ -8,7 +7,5 @@ hipError_t launch_rollout_quad6(const DevParams& p, const StepArgs& a, size_t ld
 {
     return launch_rollout_m<MPPI_QUAD6>(p, a, lds, s);
 }
-
-BatchRolloutKernel batch_rollout_kernel_quad6(int key) { return batch_kernel_of<MPPI_QUAD6>(key); }
 
 }  // namespace dbas

@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "mppi_field.hpp"
 #include "mppi_internal.hpp"
 #include "mppi_runtime.hpp"
 
@@ -264,6 +265,7 @@ mppi_ctrl::~mppi_ctrl()
     if (stream) (void)hipStreamSynchronize(stream);
     for (void* ptr : allocations) (void)hipFree(ptr);
     if (d_obs) (void)hipFree(d_obs);
+    if (d_field) (void)hipFree(d_field);
     if (d_sdf) (void)hipFree(d_sdf);
     if (d_sdf4) (void)hipFree(d_sdf4);
     if (h_res) (void)hipHostFree(h_res);
@@ -564,6 +566,8 @@ int mppi_ctrl::retile()
     return alloc_tile_buffers();
 }
 
+float mppi_ctrl::field_margin() const { return dbas::field_margin(p.model, p.P, p.shape_kind, p.cost_mode, p.shape); }
+
 extern "C" int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int32_t mem)
 {
     CHECK_HANDLE(h);
@@ -593,7 +597,13 @@ extern "C" int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int3
     }
     h->p.obs = h->d_obs;
     h->p.J = J;
+    h->p.field = nullptr;
     ++h->version;
+    if (field_wanted(h->p.model, h->cfg.K, h->cfg.T, J, h->p.P, h->p.shape_kind, h->p.cost_mode)) {
+        if (!h->d_field) HIP_TRY(h, hipMalloc(&h->d_field, kFieldBytes));
+        HIP_TRY(h, launch_field(h->d_obs, J, h->field_margin(), h->d_field, h->stream));
+        h->p.field = static_cast<const FieldHeader*>(h->d_field);
+    }
     return h->retile();
 }
 

@@ -23,6 +23,7 @@ struct mppi_ctrl {
     std::vector<void*> allocations;
     float* d_obs = nullptr;
     int obs_cap = 0;
+    void* d_field = nullptr;         // the obstacles' far field (mppi_field.hpp)
     float* d_sdf = nullptr;
     size_t sdf_bytes = 0;
     float4* d_sdf4 = nullptr;        // four-texel records of the costmap
@@ -46,6 +47,8 @@ struct mppi_ctrl {
     int configure_tiles(int S);
     int alloc_tile_buffers();
     int retile();
+    // how far from a pose the barrier's points lie, for the far field
+    float field_margin() const;
     int launch_step(const float* x0_host, const float* x0_dev, float* u0_dev, bool mark = false);
 };
 

@@ -419,6 +419,9 @@ extern "C" int mppi_server_add_robot(mppi_server_t* s, const mppi_config* cfg, i
         return s->fail(st, std::string("add_robot: ") + global_error());
     }
     st = mppi_set_obstacles(h, J, cxcyr, MPPI_MEM_HOST);
+    // the robot's launches run on any of the server's streams: what was put
+    // on this one (the obstacles' far field) is complete before the first
+    if (!st) st = h->sync();
     if (st) {
         std::lock_guard<std::mutex> lk(s->mu);
         s->fail(st, "add_robot: " + h->err);
