@@ -216,7 +216,10 @@ extern "C" int mppi_batch_step(mppi_batch_t* b, const float* x0s, float* u0s, in
         in.parity = b->ctrls[c]->iter & 1u;
     }
     if ((st = b->hip(hipGraphLaunch(b->exec, b->stream), "hipGraphLaunch"))) return st;
-    for (mppi_ctrl* h : b->ctrls) ++h->iter;
+    for (mppi_ctrl* h : b->ctrls) {
+        ++h->iter;
+        h->plan_ready = false;
+    }
     if ((st = b->hip(hipStreamSynchronize(b->stream), "hipStreamSynchronize"))) return st;
     int first = MPPI_OK;
     for (int c = 0; c < n; ++c) {

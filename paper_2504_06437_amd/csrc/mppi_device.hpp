@@ -431,7 +431,7 @@ struct TileLds {
     float* py;
     float* vx;        // velocity (quadrotors)
     float* vy;
-    float* b;         // fused barrier (indicator: smallest h), then the barrier state
+    float* b;         // fused barrier (indicator: smallest h)
     float* mp;        // costmap terms: sum B(sdf) or, with the indicator, the smallest sdf
     float2* nz;       // [T][S] the tile's noise, when it fits (else null)
 };
@@ -1075,8 +1075,7 @@ __device__ __forceinline__ float map_terms(const DevParams& p, int P, float4 pos
 //   1  inputs of the chunk (the waves that own no sample; every wave in the
 //      first chunk); meanwhile the owner lanes run the barrier-state
 //      recursion of the chunk before;
-//   2  headings (owner lanes); the others add up the chunk before's barrier
-//      costs;
+//   2  headings (owner lanes);
 //   3  sines and cosines of the headings, their tracking cost;
 //   4  positions (two lanes per sample, one an axis);
 //   5  the rest of the tracking cost, then the barrier and costmap units.
@@ -1242,8 +1241,8 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // What a recurrence carries from one chunk to the next, in the space of
     // the partial costs: heading and companion by chunk parity, barrier state.
     float2* carry_h = reinterpret_cast<float2*>(L.red);     // [2][kMaxTile]
-    float* carry_b = reinterpret_cast<float*>(L.red) + 4 * kMaxTile;
-    static_assert(5 * kMaxTile * 4 <= kRollBlock * 8, "carry");
+    double* carry_b = L.red + 2 * kMaxTile;
+    static_assert(3 * kMaxTile <= kRollBlock, "carry");
 
     // the noise of sample kk at step t (Sec. IV-C mixture, scaled per Alg. 1)
     auto noise_of = [&](uint4 r) __attribute__((always_inline)) {
@@ -1536,31 +1535,26 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         if constexpr (MAP) b = IND ? fminf(b, L.mp[idx]) : b + L.mp[idx];
         return b;
     };
-    // barrier-state recursion over chunk c (owner lanes), in place
+    // barrier-state recursion over chunk c (owner lanes) and its cost, in FP64
+    // (a body in contact has barriers of 1e4 and more, where FP32 rounds the
+    // state by what separates the samples); with the indicator, the weight of
+    // every step that violates a constraint
     auto beta_phase = [&](int c, int n) __attribute__((always_inline)) {
-        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
-        if constexpr (!IND) {
-            float beta = c == 0 ? barrier_at(n * RS) : carry_b[tid];      // (from beta_0)
-            walk(
-                n, [&](int tt) __attribute__((always_inline)) { return barrier_at(tt * RS + tid); },
-                [&](int tt, float b) __attribute__((always_inline)) {
-                    beta = fmaf(p.gamma_b, beta, b);
-                    L.b[tt * RS + tid] = beta;
-                });
-            if (c + 1 < nch) carry_b[tid] = beta;
-        }
-    };
-    // R_B beta of every item (with the indicator, the weight of every step
-    // that violates a constraint), over threads [first, block)
-    auto beta_cost = [&](int n, int first) __attribute__((always_inline)) {
-        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
-        for (int idx = tid - first; idx < n * S; idx += kRollBlock - first) {
-            if constexpr (IND) {
-                if (barrier_at(slot(idx)) < 0.0f) cost += (double)p.collision_weight;
-            } else {
-                cost += (double)p.r_b * (double)L.b[slot(idx)];
-            }
-        }
+        const int tid = phase_tid();
+        const double g = (double)p.gamma_b, w = IND ? (double)p.collision_weight : (double)p.r_b;
+        double beta = 0.0;
+        if constexpr (!IND) beta = c == 0 ? (double)barrier_at(n * RS) : carry_b[tid];      // (from beta_0)
+        walk(
+            n, [&](int tt) __attribute__((always_inline)) { return barrier_at(tt * RS + tid); },
+            [&](int, float b) __attribute__((always_inline)) {
+                if constexpr (IND) {
+                    cost += b < 0.0f ? w : 0.0;
+                } else {
+                    beta = fma(g, beta, (double)b);
+                    cost = fma(w, beta, cost);
+                }
+            });
+        if (!IND && c + 1 < nch) carry_b[tid] = beta;
     };
 
     for (int c = 0; c < nch; ++c) {
@@ -1574,11 +1568,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         }
         lds_barrier();
         if (tid == kRollBlock - 1) L.next[(c + 1) & 1] = 0;
-        if (wave < DW) {
-            if (owner) headings_phase(c, n);
-        } else if (c > 0) {
-            beta_cost(tc, POOL0);
-        }
+        if (owner) headings_phase(c, n);
         lds_barrier();
         sines_phase(t0, n);
         if (!IND && c == 0 && tid >= kRollBlock - kXSlots) {
@@ -1599,12 +1589,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         units_phase(c, n);
         lds_barrier();
     }
-    {
-        const int n = T - (nch - 1) * tc;
-        if (owner) beta_phase(nch - 1, n);
-        if constexpr (!IND) lds_barrier();
-        beta_cost(n, 0);
-    }
+    if (owner) beta_phase(nch - 1, T - (nch - 1) * tc);
     // the samples' costs: lanes of one sample within a wave, then the groups
     for (int m = S; m < kWave; m <<= 1) cost += __shfl_xor(cost, m);
     constexpr int RG = S < kWave ? kRollWaves : kRollBlock / S;

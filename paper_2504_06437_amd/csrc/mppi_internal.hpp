@@ -15,6 +15,7 @@ namespace dbas {
 constexpr int kWave = 64;
 constexpr int kRollBlock = 1024;     // rollout workgroup: 16 wave64s, one tile of S samples
 constexpr int kUpdBlock = 256;       // update workgroup: 4 wave64s, one control row each
+constexpr int kUpdAllBlock = 1024;   // update workgroup that holds every row
 constexpr int kMaxTiles = 4096;      // most sample tiles per controller
 constexpr int kMaxTile = 256;        // largest S
 constexpr int kM = MPPI_M;
@@ -90,7 +91,13 @@ struct DevParams {
     double* partN;           // [2T][tiles] tile sums of e_k du[t][c][k]
     CtrlState* st;
     HostResult* res;         // device-visible pointer to pinned host memory (may be null)
+    float* plan;             // [T][2] the same for U* (see update_publishes_plan)
 };
+
+// Does the update of a synchronous step run in one workgroup, which publishes
+// the whole plan to the host?  Up to 512 KiB of partial sums: at one compute
+// unit's 64 bytes a cycle, 3.4 us.
+inline bool update_publishes_plan(const DevParams& p) { return p.plan && (long)2 * p.T * p.tiles <= 65536; }
 
 // Per-launch arguments of the single-controller kernels.
 struct StepArgs {

@@ -503,14 +503,17 @@ int dbas::create_ctrl(const mppi_config* cfg, const mppi_device* dev, bool exter
         delete h;
         return st;
     }
-    e = hipHostMalloc(reinterpret_cast<void**>(&h->h_res), sizeof(HostResult), hipHostMallocMapped | hipHostMallocCoherent);
+    // the result block and, behind it, the plan
+    const size_t res_bytes = sizeof(HostResult) + sizeof(float) * (size_t)T * kM;
+    e = hipHostMalloc(reinterpret_cast<void**>(&h->h_res), res_bytes, hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p.res), h->h_res, 0);
+    if (e == hipSuccess) p.plan = reinterpret_cast<float*>(p.res + 1);
     if (e != hipSuccess) {
         set_global_error(std::string("pinned result buffer: ") + hipGetErrorString(e));
         delete h;
         return MPPI_E_NOMEM;
     }
-    std::memset(h->h_res, 0, sizeof(HostResult));
+    std::memset(h->h_res, 0, res_bytes);
 
     CtrlState s0;
     std::memset(&s0, 0, sizeof s0);
@@ -695,6 +698,7 @@ int mppi_ctrl::launch_step(const float* x0_host, const float* x0_dev, float* u0_
     StepArgs a;
     std::memset(&a, 0, sizeof a);
     a.mark = mark ? 1u : 0u;
+    plan_ready = false;
     if (x0_host) std::memcpy(a.x0, x0_host, sizeof(float) * p.n);
     a.x0_ptr = x0_dev;
     a.u0_dev = u0_dev;
@@ -709,6 +713,7 @@ int mppi_ctrl::launch_step(const float* x0_host, const float* x0_dev, float* u0_
     HIP_TRY(this, launch_rollout(p, a, stream));
     if (ev) HIP_TRY(this, hipEventRecord(ev[1], stream));
     HIP_TRY(this, launch_update(p, a, stream));
+    plan_published = mark && update_publishes_plan(p);
     if (p.adaptive) HIP_TRY(this, launch_explore(p, a, stream));
     ++iter;
     if (ev) HIP_TRY(this, hipEventRecord(ev[2], stream));
@@ -768,6 +773,7 @@ extern "C" int mppi_step(mppi_t* h, const float* x0, float* u0)
     // status; spin on it (a stream synchronisation wakes up later), and fall
     // back to the synchronisation -- which also reports errors -- after 50 ms
     if (!wait_completion(h->h_res, h->iter)) HIP_TRY(h, hipStreamSynchronize(h->stream));
+    h->plan_ready = h->plan_published;
     const HostResult* r = h->h_res;
     u0[0] = r->u0[0];
     u0[1] = r->u0[1];
@@ -808,6 +814,10 @@ extern "C" int mppi_get_last_optimal(mppi_t* h, float* Ustar)
 {
     CHECK_HANDLE(h);
     if (!Ustar) return MPPI_E_INVALID;
+    if (h->plan_ready) {        // a synchronous step has just waited for it
+        std::memcpy(Ustar, h->h_res + 1, sizeof(float) * (size_t)h->cfg.T * kM);
+        return MPPI_OK;
+    }
     int s = h->sync();
     if (s) return s;
     HIP_TRY(h, hipMemcpy(Ustar, h->p.Ustar, sizeof(float) * h->cfg.T * kM, hipMemcpyDeviceToHost));

@@ -28,7 +28,9 @@ struct mppi_ctrl {
     size_t sdf_bytes = 0;
     float4* d_sdf4 = nullptr;        // four-texel records of the costmap
     size_t sdf4_bytes = 0;
-    dbas::HostResult* h_res = nullptr;
+    dbas::HostResult* h_res = nullptr;   // pinned: the result block, then the plan [T][2]
+    bool plan_published = false;         // the last launch writes its U* there
+    bool plan_ready = false;             // ... and the host has seen its completion mark
     // kernel timing (mppi_profile_*): event triples per recorded iteration
     bool profiling = false;
     int prof_every = 1;                    // record every n-th iteration
