@@ -413,6 +413,7 @@ hipError_t launch_batch_update(const DevParams* d_params, const RowUnit* d_units
 hipError_t launch_explore(const DevParams& p, const StepArgs& a, hipStream_t s);
 hipError_t launch_batch_explore(const DevParams* d_params, const int32_t* d_ids, int n, const BatchIn* d_in,
                                 size_t lds, hipStream_t s);
+hipError_t launch_upload(void* dst, const void* src, size_t words, hipStream_t s);
 hipError_t launch_weights(const DevParams& p, double* d_w, hipStream_t s);
 hipError_t launch_philox_words(const DevParams& p, uint64_t counter, uint32_t* d_words, hipStream_t s);
 hipError_t launch_sdf_cells(const float* sdf, int W, int H, float4* out, hipStream_t s);

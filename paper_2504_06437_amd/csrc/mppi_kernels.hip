@@ -361,6 +361,13 @@ __global__ __launch_bounds__(256) void k_sdf_cells(const float* __restrict__ sdf
     out[idx] = make_float4(r0[0], r0[1], r0[W], r0[W + 1]);
 }
 
+// Words from pinned host memory to the device, in stream order.
+__global__ __launch_bounds__(256) void k_upload(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, int n)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
 // w_k = e_k f_b(k) / eta: the weights the update used.
 __global__ __launch_bounds__(256) void k_weights(DevParams p, double* w)
 {
@@ -916,6 +923,13 @@ hipError_t launch_batch_explore(const DevParams* d_params, const int32_t* d_ids,
                                 size_t lds, hipStream_t s)
 {
     hipLaunchKernelGGL(k_batch_explore, dim3(n), dim3(kExpBlock), lds, s, d_params, d_ids, d_in);
+    return hipGetLastError();
+}
+
+hipError_t launch_upload(void* dst, const void* src, size_t words, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_upload, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, static_cast<uint32_t*>(dst),
+                       static_cast<const uint32_t*>(src), (int)words);
     return hipGetLastError();
 }
 

@@ -28,9 +28,21 @@ struct mppi_ctrl {
     size_t sdf_bytes = 0;
     float4* d_sdf4 = nullptr;        // four-texel records of the costmap
     size_t sdf4_bytes = 0;
-    dbas::HostResult* h_res = nullptr;   // pinned: the result block, then the plan [T][2]
+    dbas::HostResult* h_res = nullptr;   // pinned: the result block, the plan [T][2], the staging
     bool plan_published = false;         // the last launch writes its U* there
     bool plan_ready = false;             // ... and the host has seen its completion mark
+    // Pinned staging of the host's inputs: an upload takes the next bytes of it
+    // and a kernel on the stream fetches them, so neither call nor caller waits.
+    // The bytes are free again once the stream is known to be past the kernel
+    // (a synchronisation, or a step's completion mark).
+    static constexpr size_t kStageBytes = 32768;
+    static_assert(kStageBytes >= sizeof(float) * 3 * MPPI_JMAX &&
+                  kStageBytes >= sizeof(float) * (MPPI_TMAX + 1) * MPPI_NMAX + 64, "an input fits");
+    char* h_stage = nullptr;             // (in the allocation of h_res)
+    char* d_stage = nullptr;             // the device's address of it
+    size_t stage_used = 0;
+    int begin_upload();
+    int upload(void* dst, const void* src, size_t bytes);
     // kernel timing (mppi_profile_*): event triples per recorded iteration
     bool profiling = false;
     int prof_every = 1;                    // record every n-th iteration

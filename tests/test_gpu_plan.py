@@ -1,0 +1,62 @@
+"""What a control period moves between host and device: the plan a synchronous
+step publishes is the one on the device (exactly: U of the next step is its
+shift), on both sides of the rule that lets one workgroup do the update; and
+inputs set any number of times between steps, past the end of their staging,
+leave the step what a fresh controller makes of the last ones (exactly: the
+same kernels on the same inputs)."""
+import numpy as np
+import pytest
+
+from paper_2504_06437_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _controller(wl, **over):
+    from paper_2504_06437_amd.controller import Controller
+    c = Controller(dict(wl["params"], **over))
+    c.load_workload(wl)
+    return c
+
+
+# (one workgroup up to 65536 tile sums, 2 T K / 16 here)
+@pytest.mark.parametrize("K,T", [(1, 1), (5232, 100), (5233, 100), (700, 31)])
+def test_published_plan_is_the_devices(K, T):
+    from paper_2504_06437_amd.hip import DeviceArray
+    wl = W.quad_large(K=K, T=T, J=40, with_map=False)
+    c = _controller(wl, tile_samples=16)
+
+    def consistent(plan):
+        assert np.array_equal(c.controls(), np.concatenate([plan[1:], plan[-1:]]))
+
+    u0 = c.step(wl["x0"])
+    plan = c.last_optimal()
+    assert np.array_equal(plan[0], u0)
+    consistent(plan)
+    x0 = DeviceArray.from_numpy(wl["x0"])
+    c.step_async(x0.at(0))
+    assert c.synchronize() == 0
+    other = c.last_optimal()
+    consistent(other)
+    assert K == 1 or not np.array_equal(other, plan)
+    c.step(wl["x0"])
+    consistent(c.last_optimal())
+    c.close()
+
+
+@pytest.mark.parametrize("J", [3, 60, 2000])
+def test_inputs_set_many_times_between_steps(J):
+    rng = np.random.default_rng(J)
+    wl = W.quad_large(K=512, T=20, J=J, with_map=False)
+    c, fresh = _controller(wl), _controller(wl)
+    for period in range(3):
+        for _ in range(40):
+            c.set_reference(rng.standard_normal(wl["x_ref"].shape).astype(np.float32))
+            c.set_obstacles(np.abs(rng.standard_normal((J, 3))).astype(np.float32) + np.float32([50, 50, 0]))
+            c.set_obstacles(wl["obstacles"])
+        c.set_reference(wl["x_ref"])
+        assert np.array_equal(c.step(wl["x0"]), fresh.step(wl["x0"]))
+        assert np.array_equal(c.last_optimal(), fresh.last_optimal())
+        assert np.array_equal(c.costs(), fresh.costs())
+    c.close()
+    fresh.close()
