@@ -335,18 +335,18 @@ template <> struct Model<MPPI_QUAD6> {
         f0 = (F1 + F2) / p.mass;
         f1 = (F2 - F1) * (p.arm / p.inertia);
     }
-    __device__ static __forceinline__ float heading(float dt, float& th, float& w, float, float f1)
+    __device__ static __forceinline__ float heading(double dt, double& th, double& w, float, float f1)
     {
-        th = fmaf(w, dt, th);
-        w = fmaf(f1, dt, w);
-        return w;
+        th = fma(w, dt, th);
+        w = fma((double)f1, dt, w);
+        return (float)w;
     }
-    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float f0, float,
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, double& q, double& v, float f0, float,
                                                     float sn, float cs)
     {
         const float a = axis == 0 ? -(f0 * sn) : fmaf(f0, cs, -p.gravity);
-        q = fmaf(v, p.dt, q);
-        v = fmaf(a, p.dt, v);
+        q = fma(v, (double)p.dt, q);
+        v = fma((double)a, (double)p.dt, v);
     }
 };
 
@@ -360,12 +360,12 @@ template <> struct Model<MPPI_QUAD5> {
         f0 = s0;
         f1 = (p.mass * p.gravity + s1) / p.mass;
     }
-    __device__ static __forceinline__ float heading(float dt, float& th, float&, float f0, float f1)
+    __device__ static __forceinline__ float heading(double dt, double& th, double&, float f0, float f1)
     {
-        th = fmaf(f0, dt, th);
+        th = fma((double)f0, dt, th);
         return f1;
     }
-    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float, float f1,
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, double& q, double& v, float, float f1,
                                                     float sn, float cs)
     {
         Model<MPPI_QUAD6>::position(p, axis, q, v, f1, 0.0f, sn, cs);
@@ -384,17 +384,17 @@ template <> struct Model<MPPI_CAR> {
         f0 = sp / (cp * p.wheelbase);
         f1 = s1;
     }
-    __device__ static __forceinline__ float heading(float dt, float& th, float& v, float f0, float f1)
+    __device__ static __forceinline__ float heading(double dt, double& th, double& v, float f0, float f1)
     {
-        th = fmaf(v * f0, dt, th);
-        v = fmaf(f1, dt, v);
-        return v;
+        th = fma(v * (double)f0, dt, th);
+        v = fma((double)f1, dt, v);
+        return (float)v;
     }
-    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float, float vn,
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, double& q, double& v, float, float vn,
                                                     float sn, float cs)
     {
-        q = fmaf(v * (axis == 0 ? cs : sn), p.dt, q);
-        v = vn;
+        q = fma((double)((float)v * (axis == 0 ? cs : sn)), (double)p.dt, q);
+        v = (double)vn;
     }
 };
 
@@ -1306,7 +1306,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         constexpr int W = Model<MODEL>::W;
         float4* a = L.a + tid;
-        float th = xs.v[2], hw = W ? xs.v[W] : 0.0f;
+        double th = xs.v[2], hw = W ? xs.v[W] : 0.0f;
         if (c > 0) {
             const float2 h = carry_h[((c - 1) & 1) * kMaxTile + tid];
             th = h.x;
@@ -1315,17 +1315,17 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         walk(
             n, [&](int tt) __attribute__((always_inline)) { return make_float2(a[tt * RS].x, a[tt * RS].y); },
             [&](int tt, float2 in) __attribute__((always_inline)) {
-                const float y = Model<MODEL>::heading(p.dt, th, hw, in.x, in.y);
-                a[tt * RS] = make_float4(in.x, y, th, 0.0f);
+                const float y = Model<MODEL>::heading((double)p.dt, th, hw, in.x, in.y);
+                a[tt * RS] = make_float4(in.x, y, (float)th, 0.0f);
             });
         if (c + 1 < nch) {
-            carry_h[(c & 1) * kMaxTile + tid] = make_float2(th, hw);
+            carry_h[(c & 1) * kMaxTile + tid] = make_float2((float)th, (float)hw);
         } else {
             const float* rf = L.ref + T * NS;
-            const float d2 = th - rf[2];
+            const float d2 = (float)th - rf[2];
             float f = p.Qf[2] * (d2 * d2);
             if constexpr (W != 0) {
-                const float dw = hw - rf[W];
+                const float dw = (float)hw - rf[W];
                 f = fmaf(p.Qf[W], dw * dw, f);
             }
             cost += (double)f;
@@ -1361,7 +1361,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         const float4* a = L.a + s_mine;
         float* pos = (axis == 0 ? L.px : L.py) + s_mine;
         [[maybe_unused]] float* vel = (axis == 0 ? L.vx : L.vy) + s_mine;
-        float q = 0.0f, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
+        double q = 0.0, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
         float th = xs.v[2];
         if (c > 0) {        // (this lane's own last step of the chunk before)
             const float2 h = carry_h[((c - 1) & 1) * kMaxTile + s_mine];
@@ -1378,15 +1378,15 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 Model<MODEL>::position(p, axis, q, v, in.x, in.y, sn, cs);
                 sn = in.z;
                 cs = in.w;
-                pos[tt * RS] = q;
-                if constexpr (NS > 4) vel[tt * RS] = v;
+                pos[tt * RS] = (float)q;
+                if constexpr (NS > 4) vel[tt * RS] = (float)v;
             });
         if (c + 1 == nch) {
             const float* rf = L.ref + T * NS;
-            const float d0 = q - rf[axis];
+            const float d0 = (float)q - rf[axis];
             float f = p.Qf[axis] * (d0 * d0);
             if constexpr (NS > 4) {
-                const float d3 = v - rf[3 + axis];
+                const float d3 = (float)v - rf[3 + axis];
                 f = fmaf(p.Qf[3 + axis], d3 * d3, f);
             }
             cost += (double)f;
