@@ -476,6 +476,8 @@ __device__ __forceinline__ TileLds carve(unsigned char* smem, int J, int T, int 
 struct X0 {
     float v[MPPI_NMAX + 2];
     uint32_t parity;     // which half of the warm-start double buffer holds U
+    float S_e;           // exploration rate
+    uint64_t counter;    // Philox step counter
 };
 
 constexpr int kRollWaves = kRollBlock / kWave;
@@ -1109,9 +1111,8 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     const int nch = (T + tc - 1) / tc;
     const bool keep_noise = tile_keeps_noise(J, T, NS, S);
     const TileLds L = carve(smem, J, T, NS, S, tc, keep_noise);
-    const CtrlState* cs_in = p.st;
-    const float S_e = cs_in->S_e;
-    const uint64_t ctr = cs_in->counter;
+    const float S_e = xs.S_e;
+    const uint64_t ctr = xs.counter;
     const uint32_t c_lo = (uint32_t)ctr, c_hi = (uint32_t)(ctr >> 32);
 
     // the Philox words of sample kk at step t (Sec. IV-C: counter (k, t, iteration))
@@ -1818,6 +1819,9 @@ __global__ __launch_bounds__(kRollBlock) void k_rollout(DevParams p, StepArgs a)
         for (int i = 0; i < MPPI_NMAX + 2; ++i) xs.v[i] = a.x0[i];
     }
     xs.parity = a.parity;
+    const bool own = a.S_e > 0.0f;
+    xs.S_e = own ? a.S_e : p.st->S_e;
+    xs.counter = own ? a.counter : p.st->counter;
     rollout_tile<MODEL, S, PT, IND, MAP, FIELD>(p, xcd_tile((int)blockIdx.x, p.tiles), xs, smem);
 }
 
@@ -1844,6 +1848,8 @@ __global__ __launch_bounds__(kRollBlock) void k_batch_rollout(const DevParams* _
 #pragma unroll
         for (int i = 0; i < MPPI_NMAX + 2; ++i) xs.v[i] = in[bu.ctrl].x0[i];
         xs.parity = in[bu.ctrl].parity;
+        xs.S_e = p.st->S_e;
+        xs.counter = p.st->counter;
         rollout_tile<MODEL, S, PT, IND, MAP, FIELD>(p, bu.tile, xs, smem);
         __syncthreads();
     }

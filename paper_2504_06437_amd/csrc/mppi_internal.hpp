@@ -108,6 +108,8 @@ struct StepArgs {
     uint32_t mark;           // 1: publish u0, status and the completion mark to the host
                              //    at once (system-scope fences), for a host thread spinning
     int32_t* status_dev;     // optional device copy of the iteration's status
+    uint64_t counter;        // of a call without a handle: its Philox step counter
+    float S_e;               // and exploration rate (0: both are in p.st)
 };
 
 // Per-step input of one controller of a batch (staged by the host).
