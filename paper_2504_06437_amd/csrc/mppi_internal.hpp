@@ -15,7 +15,6 @@ namespace dbas {
 constexpr int kWave = 64;
 constexpr int kRollBlock = 1024;     // rollout workgroup: 16 wave64s, one tile of S samples
 constexpr int kUpdBlock = 256;       // update workgroup: 4 wave64s, one control row each
-constexpr int kUpdAllBlock = 1024;   // update workgroup that holds every row
 constexpr int kMaxTiles = 4096;      // most sample tiles per controller
 constexpr int kMaxTile = 256;        // largest S
 constexpr int kM = MPPI_M;
@@ -91,13 +90,8 @@ struct DevParams {
     double* partN;           // [2T][tiles] tile sums of e_k du[t][c][k]
     CtrlState* st;
     HostResult* res;         // device-visible pointer to pinned host memory (may be null)
-    float* plan;             // [T][2] the same for U* (see update_publishes_plan)
+    uint64_t* plan;          // [T][2] the same for U*: (iteration << 32) | the value's bits
 };
-
-// Does the update of a synchronous step run in one workgroup, which publishes
-// the whole plan to the host?  Up to 512 KiB of partial sums: at one compute
-// unit's 64 bytes a cycle, 3.4 us.
-inline bool update_publishes_plan(const DevParams& p) { return p.plan && (long)2 * p.T * p.tiles <= 65536; }
 
 // Per-launch arguments of the single-controller kernels.
 struct StepArgs {
@@ -107,6 +101,7 @@ struct StepArgs {
     uint32_t parity;         // iterations run & 1: the half of U that holds the warm start
     uint32_t mark;           // 1: publish u0, status and the completion mark to the host
                              //    at once (system-scope fences), for a host thread spinning
+    uint32_t seq;            // the iteration the published plan is marked with
     int32_t* status_dev;     // optional device copy of the iteration's status
     uint64_t counter;        // of a call without a handle: its Philox step counter
     float S_e;               // and exploration rate (0: both are in p.st)

@@ -53,6 +53,25 @@ bool wait_completion(const HostResult* r, uint64_t want)
     }
 }
 
+// The plan that a synchronous step publishes, word by word as each arrives
+// (the step's own mark stands for the rows of u0 alone; the others are written
+// at about the same time); false if one does not within 50 ms.  Against the
+// stream's synchronisation and a copy, 10 us less.
+bool read_plan(const uint64_t* plan, int n, uint32_t want, float* out)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int r = 0; r < n; ++r) {
+        uint64_t w;
+        for (uint32_t i = 1; (uint32_t)((w = *(const volatile uint64_t*)(plan + r)) >> 32) != want; ++i) {
+            if ((i & 1023u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) return false;
+            __builtin_ia32_pause();
+        }
+        const uint32_t bits = (uint32_t)w;
+        std::memcpy(out + r, &bits, sizeof bits);
+    }
+    return true;
+}
+
 // Savitzky-Golay weights for every step of a horizon of T: row t holds the
 // 2m+1 weights a_j with which the smoothed value at t is sum_j a_j y[s + j],
 // s = clamp(t - m, 0, T - 2m - 1): the value at t of the least-squares
@@ -533,12 +552,12 @@ int dbas::create_ctrl(const mppi_config* cfg, const mppi_device* dev, bool exter
         return st;
     }
     // the result block and, behind it, the plan and the staging
-    const size_t res_bytes = (sizeof(HostResult) + sizeof(float) * (size_t)T * kM + 63) & ~(size_t)63;
+    const size_t res_bytes = (sizeof(HostResult) + sizeof(uint64_t) * (size_t)T * kM + 63) & ~(size_t)63;
     e = hipHostMalloc(reinterpret_cast<void**>(&h->h_res), res_bytes + mppi_ctrl::kStageBytes,
                       hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p.res), h->h_res, 0);
     if (e == hipSuccess) {
-        p.plan = reinterpret_cast<float*>(p.res + 1);
+        p.plan = reinterpret_cast<uint64_t*>(p.res + 1);
         h->h_stage = reinterpret_cast<char*>(h->h_res) + res_bytes;
         h->d_stage = reinterpret_cast<char*>(p.res) + res_bytes;
     }
@@ -737,6 +756,7 @@ int mppi_ctrl::launch_step(const float* x0_host, const float* x0_dev, float* u0_
     StepArgs a;
     std::memset(&a, 0, sizeof a);
     a.mark = mark ? 1u : 0u;
+    a.seq = (uint32_t)(iter + 1);
     plan_ready = false;
     if (x0_host) std::memcpy(a.x0, x0_host, sizeof(float) * p.n);
     a.x0_ptr = x0_dev;
@@ -752,7 +772,6 @@ int mppi_ctrl::launch_step(const float* x0_host, const float* x0_dev, float* u0_
     HIP_TRY(this, launch_rollout(p, a, stream));
     if (ev) HIP_TRY(this, hipEventRecord(ev[1], stream));
     HIP_TRY(this, launch_update(p, a, stream));
-    plan_published = mark && update_publishes_plan(p);
     if (p.adaptive) HIP_TRY(this, launch_explore(p, a, stream));
     ++iter;
     if (ev) HIP_TRY(this, hipEventRecord(ev[2], stream));
@@ -813,7 +832,7 @@ extern "C" int mppi_step(mppi_t* h, const float* x0, float* u0)
     // back to the synchronisation -- which also reports errors -- after 50 ms
     if (!wait_completion(h->h_res, h->iter)) HIP_TRY(h, hipStreamSynchronize(h->stream));
     h->stage_used = 0;          // every upload came before the step
-    h->plan_ready = h->plan_published;
+    h->plan_ready = true;
     const HostResult* r = h->h_res;
     u0[0] = r->u0[0];
     u0[1] = r->u0[1];
@@ -854,10 +873,9 @@ extern "C" int mppi_get_last_optimal(mppi_t* h, float* Ustar)
 {
     CHECK_HANDLE(h);
     if (!Ustar) return MPPI_E_INVALID;
-    if (h->plan_ready) {        // a synchronous step has just waited for it
-        std::memcpy(Ustar, h->h_res + 1, sizeof(float) * (size_t)h->cfg.T * kM);
+    if (h->plan_ready && read_plan(reinterpret_cast<const uint64_t*>(h->h_res + 1), h->cfg.T * kM, (uint32_t)h->iter,
+                                   Ustar))
         return MPPI_OK;
-    }
     int s = h->sync();
     if (s) return s;
     HIP_TRY(h, hipMemcpy(Ustar, h->p.Ustar, sizeof(float) * h->cfg.T * kM, hipMemcpyDeviceToHost));

@@ -29,8 +29,7 @@ struct mppi_ctrl {
     float4* d_sdf4 = nullptr;        // four-texel records of the costmap
     size_t sdf4_bytes = 0;
     dbas::HostResult* h_res = nullptr;   // pinned: the result block, the plan [T][2], the staging
-    bool plan_published = false;         // the last launch writes its U* there
-    bool plan_ready = false;             // ... and the host has seen its completion mark
+    bool plan_ready = false;             // the last iteration was a synchronous step: its U* is there
     // Pinned staging of the host's inputs: an upload takes the next bytes of it
     // and a kernel on the stream fetches them, so neither call nor caller waits.
     // The bytes are free again once the stream is known to be past the kernel

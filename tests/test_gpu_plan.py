@@ -1,7 +1,7 @@
 """What a control period moves between host and device: the plan a synchronous
-step publishes is the one on the device (exactly: U of the next step is its
-shift), on both sides of the rule that lets one workgroup do the update; and
-inputs set any number of times between steps, past the end of their staging,
+step publishes, row by row, is the one on the device (exactly: U of the next
+step is its shift), with one row group and many, few tiles and many; and inputs
+set any number of times between steps, past the end of their staging,
 leave the step what a fresh controller makes of the last ones (exactly: the
 same kernels on the same inputs)."""
 import numpy as np
@@ -19,7 +19,6 @@ def _controller(wl, **over):
     return c
 
 
-# (one workgroup up to 65536 tile sums, 2 T K / 16 here)
 @pytest.mark.parametrize("K,T", [(1, 1), (5232, 100), (5233, 100), (700, 31)])
 def test_published_plan_is_the_devices(K, T):
     from paper_2504_06437_amd.hip import DeviceArray
