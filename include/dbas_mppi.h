@@ -206,7 +206,8 @@ int mppi_create(const mppi_config* cfg, const mppi_device* dev, mppi_t** out);
 void mppi_destroy(mppi_t* h);
 
 /* Circular obstacles (Sec. V-A/V-B: h = |p - c|^2 - r^2): J rows of
- * (cx, cy, r), copied.  J = 0 clears them.  Errors: INVALID (J outside
+ * (cx, cy, r), copied.  With many of them and many samples the call also
+ * starts the build of their far field on the stream.  J = 0 clears them.  Errors: INVALID (J outside
  * 0..MPPI_JMAX, non-finite or negative r). */
 int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int32_t mem);
 
