@@ -15,6 +15,7 @@
 //                       - their sines and cosines, every item in parallel;
 //                       - positions: one lane per sample and axis integrates
 //                         velocity and position;
+//                       - the tracking cost, every item in parallel;
 //                       - poses: every (step, sample) is split over lanes that
 //                         each take a range of obstacles (LDS), and the costmap
 //                         -- the bulk of the work, no dependence between items;
@@ -335,18 +336,18 @@ template <> struct Model<MPPI_QUAD6> {
         f0 = (F1 + F2) / p.mass;
         f1 = (F2 - F1) * (p.arm / p.inertia);
     }
-    __device__ static __forceinline__ float heading(double dt, double& th, double& w, float, float f1)
+    __device__ static __forceinline__ float heading(float dt, float& th, float& w, float, float f1)
     {
-        th = fma(w, dt, th);
-        w = fma((double)f1, dt, w);
-        return (float)w;
+        th = fmaf(w, dt, th);
+        w = fmaf(f1, dt, w);
+        return w;
     }
-    __device__ static __forceinline__ void position(const DevParams& p, int axis, double& q, double& v, float f0, float,
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float f0, float,
                                                     float sn, float cs)
     {
         const float a = axis == 0 ? -(f0 * sn) : fmaf(f0, cs, -p.gravity);
-        q = fma(v, (double)p.dt, q);
-        v = fma((double)a, (double)p.dt, v);
+        q = fmaf(v, p.dt, q);
+        v = fmaf(a, p.dt, v);
     }
 };
 
@@ -360,12 +361,12 @@ template <> struct Model<MPPI_QUAD5> {
         f0 = s0;
         f1 = (p.mass * p.gravity + s1) / p.mass;
     }
-    __device__ static __forceinline__ float heading(double dt, double& th, double&, float f0, float f1)
+    __device__ static __forceinline__ float heading(float dt, float& th, float&, float f0, float f1)
     {
-        th = fma((double)f0, dt, th);
+        th = fmaf(f0, dt, th);
         return f1;
     }
-    __device__ static __forceinline__ void position(const DevParams& p, int axis, double& q, double& v, float, float f1,
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float, float f1,
                                                     float sn, float cs)
     {
         Model<MPPI_QUAD6>::position(p, axis, q, v, f1, 0.0f, sn, cs);
@@ -384,17 +385,17 @@ template <> struct Model<MPPI_CAR> {
         f0 = sp / (cp * p.wheelbase);
         f1 = s1;
     }
-    __device__ static __forceinline__ float heading(double dt, double& th, double& v, float f0, float f1)
+    __device__ static __forceinline__ float heading(float dt, float& th, float& v, float f0, float f1)
     {
-        th = fma(v * (double)f0, dt, th);
-        v = fma((double)f1, dt, v);
-        return (float)v;
+        th = fmaf(v * f0, dt, th);
+        v = fmaf(f1, dt, v);
+        return v;
     }
-    __device__ static __forceinline__ void position(const DevParams& p, int axis, double& q, double& v, float, float vn,
+    __device__ static __forceinline__ void position(const DevParams& p, int axis, float& q, float& v, float, float vn,
                                                     float sn, float cs)
     {
-        q = fma((double)((float)v * (axis == 0 ? cs : sn)), (double)p.dt, q);
-        v = (double)vn;
+        q = fmaf(v * (axis == 0 ? cs : sn), p.dt, q);
+        v = vn;
     }
 };
 
@@ -426,13 +427,13 @@ struct TileLds {
     float2* shape;    // [MPPI_PMAX] shape points (for lanes that differ in theirs: the kernel
                       // arguments lie in host memory, and only scalar reads of them are cached)
     // slots of one chunk, per (step, sample), and kXSlots more:
-    float4* a;        // (f0, f1), then (f0, y, sin theta, cos theta)
+    float4* a;        // (f0, f1, -, control cost), (f0, y, theta, control cost), then (f0, y, sin, cos)
     float* px;        // position, local frame
     float* py;
     float* vx;        // velocity (quadrotors)
     float* vy;
-    float* b;         // fused barrier (indicator: smallest h)
-    float* mp;        // costmap terms: sum B(sdf) or, with the indicator, the smallest sdf
+    float* b;         // theta, then the fused barrier (indicator: smallest h)
+    float* mp;        // the control cost, then the costmap terms: sum B(sdf) or, with the indicator, the smallest sdf
     float2* nz;       // [T][S] the tile's noise, when it fits (else null)
 };
 
@@ -573,9 +574,9 @@ struct AxisBody {
         for (int i = 0; i < 7; ++i) h[i] = clamp_h(h[i], eps);
         return 0.5f * reciprocal_total<7>(h);
     }
-    // Four obstacles' sum behind one wave-uniform test (a wave takes the
+    // Four obstacles' terms behind one wave-uniform test (a wave takes the
     // clamped form of an obstacle only when a lane needs it).
-    __device__ __forceinline__ float four(const float4 o0, const float4 o1, const float4 o2, const float4 o3) const
+    __device__ __forceinline__ float4 four(const float4 o0, const float4 o1, const float4 o2, const float4 o3) const
     {
         float m0, m1, m2, m3;
         float f0 = fast(o0, m0), f1 = fast(o1, m1), f2 = fast(o2, m2), f3 = fast(o3, m3);
@@ -589,7 +590,7 @@ struct AxisBody {
             if (__ballot(!k2)) { const float s = slow(o2); f2 = k2 ? f2 : s; }
             if (__ballot(!k3)) { const float s = slow(o3); f3 = k3 ? f3 : s; }
         }
-        return (f0 + f1) + (f2 + f3);
+        return make_float4(f0, f1, f2, f3);
     }
     __device__ __forceinline__ float one(const float4 o) const
     {
@@ -604,9 +605,12 @@ struct AxisBody {
     }
 };
 
-// Part of the fused barrier of one pose, lane sp of a group of js = 2^lg
-// lanes: every shape point against obstacles sp, sp + js, sp + 2 js, ...
-// below J (read from LDS).  The costmap terms are formed apart (map_terms).
+// Part of the fused barrier of one pose, lane sp of a group of 2^lg lanes:
+// every shape point against the obstacles (read from LDS) of this lane's runs.
+// Run r of the pose's js = 2^rlg takes obstacles r, r + js, r + 2 js, ... below
+// J and adds them up in that order; the lane's 2^(rlg - lg) <= 4 runs are
+// neighbours, and their sums meet in pairs, as those of the lanes do.  The
+// costmap terms are formed apart (map_terms).
 //
 // With e = pose - o, the heading u = (cos, sin) and its normal v, a shape
 // point with body offset (a, b) gives
@@ -618,26 +622,24 @@ struct AxisBody {
 // * quadrotors, every point on the body axis (b = 0): h = |e|^2 - r^2 +
 //   fma(2a, e.u, a^2), two operations a pair; when the points mirror about
 //   the centre (the paper's frame), a mirrored pair takes three operations.
-// Any other shape takes the general form (walk_points).
+// Any other shape takes the general form: h = (|e|^2 - r^2) + 2 e.d_i + |d_i|^2
+// with d_i the rotated offset, an add and two FMAs a pair.
 // (sa2, sb2) = 2 (a_i, b_i), ss = a_i^2 + b_i^2.
 template <int MODEL, int PT>
 __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const TileLds& L, const float* sa2,
                                                     const float* sb2, const float* ss, float4 pose, int sp, int lg,
-                                                    float omax2)
+                                                    int rlg, float omax2)
 {
-    static_assert(PT != 0, "the general form is walk_points");
-    constexpr int PM = PT;
+    constexpr int PM = PT ? PT : MPPI_PMAX;
     const float eps = p.h_eps;
     const float cs = pose.z, sn = pose.w;
-    float acc = 0.0f, acc2 = 0.0f;
-    const int J = p.J, js = 1 << lg;
-    // Lane sp of its group of js takes obstacles sp, sp + js, ...: q of them
-    // on every lane, and one more when sp < rem.  The loop count q is the
-    // same on every lane, so the loop is counted in scalar registers; both
+    const int J = p.J, js = 1 << rlg;
+    // A run has q obstacles, and one more when r < rem.  The loop count q is
+    // the same on every lane, so the loop is counted in scalar registers; both
     // reads of a pair are issued before either obstacle is used.
-    const int q = J >> lg, rem = J & (js - 1);
-    auto run = [&](auto&& body) __attribute__((always_inline)) {
-        const float4* ob = L.obs + sp;
+    const int q = J >> rlg, rem = J & (js - 1);
+    auto run = [&](int r, auto&& body) __attribute__((always_inline)) {
+        const float4* ob = L.obs + r;
         for (int i = 0; i + 2 <= q; i += 2) {
             const float4 o0 = ob[0], o1 = ob[js];
             ob += 2 * js;
@@ -648,27 +650,20 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
             body(ob[0]);
             ob += js;
         }
-        if (sp < rem) body(ob[0]);
+        if (r < rem) body(ob[0]);
     };
-    // The same walk adding up what the body returns, four obstacles' sum at a
-    // time, in FP64 (an FP32 running sum rounds at its own magnitude at every
-    // addition: over a hundred obstacles, ten times what their terms round at).
-    auto run_sum = [&](auto&& body, double& sum) __attribute__((always_inline)) {
-        const float4* ob = L.obs + sp;
-        int i = 0;
-        for (; i + 4 <= q; i += 4) {
-            const float4 o0 = ob[0], o1 = ob[js], o2 = ob[2 * js], o3 = ob[3 * js];
-            ob += 4 * js;
-            const float f0 = body(o0), f1 = body(o1), f2 = body(o2), f3 = body(o3);
-            sum += (double)((f0 + f1) + (f2 + f3));
+    // The sum over this lane's runs of sum(r).
+    auto over_runs = [&](auto&& sum) __attribute__((always_inline)) {
+        const int n = 1 << (rlg - lg);
+        float all = 0.0f, pair = 0.0f;
+#pragma unroll 1
+        for (int g = 0; g < n; ++g) {
+            const float w = sum(sp * n + g);
+            pair = (g & 1) ? pair + w : w;
+            if (g < 2) all = pair;
+            else if (g == 3) all += pair;
         }
-        float rest = 0.0f;
-        for (; i < q; ++i) {
-            rest += body(ob[0]);
-            ob += js;
-        }
-        if (sp < rem) rest += body(ob[0]);
-        sum += (double)rest;
+        return all;
     };
     // Pair fractions (the layout forms' fast path).  Two points whose h are
     // c + d and c - d give 1/(c+d) + 1/(c-d) = 2c/(c^2 - d^2); the bodies of
@@ -678,11 +673,43 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
     // obstacle is at least gmin = max(h_eps, 1e-4) -- then B(h) = 1/h, and
     // every h lies in [gmin, 2c] -- and c is at most the form's cap, so the
     // products of all the h stay inside the FP32 range.  Any other obstacle
-    // takes the clamped per-point form.  `half` sums c/q, half of each
+    // takes the clamped per-point form.  The sums are of c/q, half of each
     // fraction.
     const float gmin = fmaxf(eps, 1e-4f);
-    double half = 0.0;
-    if constexpr (MODEL == MPPI_CAR) {
+    if constexpr (PT == 0) {
+        // 2 d_i of every point, in registers; the rest of a pair is an add, two
+        // FMAs, the clamp and the reciprocal
+        float tx[PM], ty[PM], d2[PM];
+        const int P = p.P;
+#pragma unroll
+        for (int i = 0; i < PM; ++i) {
+            const float a = i < P ? p.shape[i][0] : 0.0f, b = i < P ? p.shape[i][1] : 0.0f;
+            tx[i] = fmaf(2.0f * a, cs, -(2.0f * b) * sn);
+            ty[i] = fmaf(2.0f * a, sn, (2.0f * b) * cs);
+            d2[i] = uniform(fmaf(a, a, b * b));
+        }
+        return over_runs([&](int r) __attribute__((always_inline)) {
+            float acc = 0.0f;
+            run(r, [&](const float4 o) __attribute__((always_inline)) {
+                const float ex = pose.x - o.x, ey = pose.y - o.y;
+                const float ee = fmaf(ex, ex, fmaf(ey, ey, o.w));
+                // two points behind one branch (the empty asm keeps it one: as
+                // selects, all 16 points were formed whatever P)
+#pragma unroll
+                for (int i = 0; i < PM; i += 2) {
+                    if (i < P) {
+                        const float h0 = clamp_h(fmaf(ex, tx[i], fmaf(ey, ty[i], ee + d2[i])), eps);
+                        const float h1 = clamp_h(fmaf(ex, tx[i + 1], fmaf(ey, ty[i + 1], ee + d2[i + 1])), eps);
+                        acc += __builtin_amdgcn_rcpf(h0);
+                        const float f1 = __builtin_amdgcn_rcpf(h1);
+                        acc += i + 1 < P ? f1 : 0.0f;
+                        asm volatile("" : "+v"(acc));
+                    }
+                }
+            });
+            return acc;
+        });
+    } else if constexpr (MODEL == MPPI_CAR) {
         static_assert(PT == 8, "vehicle layout: 8 points");
         // point 0 is (a, b); o.z = -r^2 + a^2 + b^2, so C = |e|^2 - r^2 + a^2 +
         // b^2 takes two operations, and with P = 2a e.u, Q = 2b e.v the
@@ -699,34 +726,38 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         // needs the cap term in the guard
         auto body = [&](auto nocap_tag) __attribute__((always_inline)) {
             constexpr bool NOCAP = decltype(nocap_tag)::value;
-            run_sum([&](const float4 o) __attribute__((always_inline)) {
-                const float ex = pose.x - o.x, ey = pose.y - o.y;
-                const float C = fmaf(ex, ex, fmaf(ey, ey, o.z));
-                const float Pu = fmaf(ex, cu, ey * su), Qv = fmaf(ey, cv, -ex * sv);
-                const float X1 = C + Pu, X2 = C - Pu, X3 = C - BB, X4 = C - AA;
-                const float aP = fabsf(Pu), aQ = fabsf(Qv);
-                const float g = NOCAP ? fminf(fminf(C - aP - aQ, X3 - aP), X4 - aQ)
-                                      : fminf(fminf(C - aP - aQ, X3 - aP), fminf(X4 - aQ, (kCap + gmin) - C));
-                const float P2 = Pu * Pu, Q2 = Qv * Qv;
-                const float q1 = fmaf(X1, X1, -Q2), q2 = fmaf(X2, X2, -Q2);
-                const float q3 = fmaf(X3, X3, -P2), q4 = fmaf(X4, X4, -Q2);
-                const float n12 = fmaf(X1, q2, X2 * q1), d12 = q1 * q2;
-                const float n34 = fmaf(X3, q4, X4 * q3), d34 = q3 * q4;
-                float f = fmaf(n12, d34, n34 * d12) * __builtin_amdgcn_rcpf(d12 * d34);
-                // (a wave-uniform branch: the clamped form only when a lane needs it)
-                if (__builtin_expect(__ballot(g < gmin) != 0, 0)) {
-                    float h[8] = {X1 + Qv, X1 - Qv, X2 + Qv, X2 - Qv, X1 - BB, X2 - BB, X4 + Qv, X4 - Qv};
+            return over_runs([&](int r) __attribute__((always_inline)) {
+                float half = 0.0f;
+                run(r, [&](const float4 o) __attribute__((always_inline)) {
+                    const float ex = pose.x - o.x, ey = pose.y - o.y;
+                    const float C = fmaf(ex, ex, fmaf(ey, ey, o.z));
+                    const float Pu = fmaf(ex, cu, ey * su), Qv = fmaf(ey, cv, -ex * sv);
+                    const float X1 = C + Pu, X2 = C - Pu, X3 = C - BB, X4 = C - AA;
+                    const float aP = fabsf(Pu), aQ = fabsf(Qv);
+                    const float g = NOCAP ? fminf(fminf(C - aP - aQ, X3 - aP), X4 - aQ)
+                                          : fminf(fminf(C - aP - aQ, X3 - aP), fminf(X4 - aQ, (kCap + gmin) - C));
+                    const float P2 = Pu * Pu, Q2 = Qv * Qv;
+                    const float q1 = fmaf(X1, X1, -Q2), q2 = fmaf(X2, X2, -Q2);
+                    const float q3 = fmaf(X3, X3, -P2), q4 = fmaf(X4, X4, -Q2);
+                    const float n12 = fmaf(X1, q2, X2 * q1), d12 = q1 * q2;
+                    const float n34 = fmaf(X3, q4, X4 * q3), d34 = q3 * q4;
+                    float f = fmaf(n12, d34, n34 * d12) * __builtin_amdgcn_rcpf(d12 * d34);
+                    // (a wave-uniform branch: the clamped form only when a lane needs it)
+                    if (__builtin_expect(__ballot(g < gmin) != 0, 0)) {
+                        float h[8] = {X1 + Qv, X1 - Qv, X2 + Qv, X2 - Qv, X1 - BB, X2 - BB, X4 + Qv, X4 - Qv};
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) h[i] = clamp_h(h[i], eps);
-                    const float slow = 0.5f * reciprocal_total<8>(h);
-                    f = g >= gmin ? f : slow;
-                }
-                return f;
-            }, half);
+                        for (int i = 0; i < 8; ++i) h[i] = clamp_h(h[i], eps);
+                        const float slow = 0.5f * reciprocal_total<8>(h);
+                        f = g >= gmin ? f : slow;
+                    }
+                    half += f;
+                });
+                return 2.0f * half;
+            });
         };
         const float bound = fmaf(2.0f, fmaf(pose.x, pose.x, pose.y * pose.y), omax2) + ss[0];
-        if (__ballot(!(bound <= kCap)) == 0) body(std::true_type{});
-        else body(std::false_type{});
+        if (__ballot(!(bound <= kCap)) == 0) return body(std::true_type{});
+        return body(std::false_type{});
     } else {
         static_assert(PT == 7, "quadrotor layout: 7 points");
         // The mirrored-axis form: a_{6-i} = -a_i, and |a_0| is the largest
@@ -751,25 +782,33 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
             // Four obstacles an iteration share one guard test, so the loop
             // takes no branch per obstacle.
             const AxisBody body(sa2, ss, pose, eps);
-            const float4* ob = L.obs + sp;
-            int i = 0;
-            for (; i + 4 <= q; i += 4) {
-                half += (double)body.four(ob[0], ob[js], ob[2 * js], ob[3 * js]);
-                ob += 4 * js;
-            }
-            float rest = 0.0f;
-            for (; i < q; ++i) {
-                rest += body.one(ob[0]);
-                ob += js;
-            }
-            if (sp < rem) rest += body.one(ob[0]);
-            half += (double)rest;
-        } else {
-            // (on the mirrored-axis tile o.z carries the a_0^2 offset)
-            float ssx[PM];
+            return over_runs([&](int r) __attribute__((always_inline)) {
+                float half = 0.0f;
+                const float4* ob = L.obs + r;
+                int i = 0;
+                for (; i + 4 <= q; i += 4) {
+                    const float4 f = body.four(ob[0], ob[js], ob[2 * js], ob[3 * js]);
+                    ob += 4 * js;
+                    half += f.x;
+                    half += f.y;
+                    half += f.z;
+                    half += f.w;
+                }
+                for (; i < q; ++i) {
+                    half += body.one(ob[0]);
+                    ob += js;
+                }
+                if (r < rem) half += body.one(ob[0]);
+                return 2.0f * half;
+            });
+        }
+        // (on the mirrored-axis tile o.z carries the a_0^2 offset)
+        float ssx[PM];
 #pragma unroll
-            for (int i = 0; i < PM; ++i) ssx[i] = mirrored ? ss[i] - ss[0] : ss[i];
-            run([&](const float4 o) __attribute__((always_inline)) {
+        for (int i = 0; i < PM; ++i) ssx[i] = mirrored ? ss[i] - ss[0] : ss[i];
+        return over_runs([&](int r) __attribute__((always_inline)) {
+            float acc = 0.0f, acc2 = 0.0f;
+            run(r, [&](const float4 o) __attribute__((always_inline)) {
                 const float ex = pose.x - o.x, ey = pose.y - o.y;
                 const float ee = fmaf(ex, ex, fmaf(ey, ey, o.z));
                 const float pu = fmaf(ex, cs, ey * sn);
@@ -778,9 +817,9 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
                 for (int i = 0; i < PM; ++i) h[i] = clamp_h(ee + fmaf(sa2[i], pu, ssx[i]), eps);
                 reciprocal_sum<PM>(h, acc, acc2);
             });
-        }
+            return acc + acc2;
+        });
     }
-    return (float)(2.0 * half + (double)(acc + acc2));
 }
 
 // The general form of one pose against all obstacles, lane sp of a group of
@@ -962,7 +1001,8 @@ __device__ __forceinline__ float field_barrier_axis(const DevParams& p, const Ti
             // (beyond the list's end: the group's first obstacle again, taken off below)
             const int i1 = left > 1 ? w.x >> 16 : i0, i2 = left > 2 ? w.y & 0xFFFF : i0, i3 = left > 3 ? w.y >> 16 : i0;
             if (__ballot(left < 4) == 0) {
-                half += body.four(L.obs[i0], L.obs[i1], L.obs[i2], L.obs[i3]);
+                const float4 f = body.four(L.obs[i0], L.obs[i1], L.obs[i2], L.obs[i3]);
+                half += (f.x + f.y) + (f.z + f.w);
             } else {
                 const float f0 = body.one(L.obs[i0]), f1 = body.one(L.obs[i1]);
                 const float f2 = body.one(L.obs[i2]), f3 = body.one(L.obs[i3]);
@@ -1078,15 +1118,23 @@ __device__ __forceinline__ float map_terms(const DevParams& p, int P, float4 pos
 //      first chunk); meanwhile the owner lanes run the barrier-state
 //      recursion of the chunk before;
 //   2  headings (owner lanes);
-//   3  sines and cosines of the headings, their tracking cost;
+//   3  sines and cosines of the headings;
 //   4  positions (two lanes per sample, one an axis);
-//   5  the rest of the tracking cost, then the barrier and costmap units.
+//   5  the tracking cost;
+//   6  the barrier and costmap units.
 // Measured: carrying the whole dynamics step on one lane per sample (the
 // sine, the tracking cost and a compensated sum among it) took 0.3 us a
 // step; the recurrences alone take about 0.03.
-// Every (step, sample) of a chunk is split over nsp adjacent lanes; lane sp
-// of the group takes obstacles sp, sp + nsp, ..., so a wave's lanes read one
-// contiguous run of obstacles at a time; the nsp partial sums meet by wave
+// A plan is the next period's warm start, and samples that nearly tie share the
+// weights, so the rounding of a cost grows from period to period.  What rounds
+// it is therefore held whatever the chunks, lanes and waves: the state in FP32,
+// a step's tracking and control cost one FP32 sum over the state in order, the
+// barrier state in FP32, the obstacles' runs (set_splits).  Those FP32 terms
+// are added up in FP64, where the order is below the rest.  (Recurrences and
+// barrier sums in FP64, closer to the exact costs, moved plans of the second
+// period by up to 4e-4.)
+// Every (step, sample) of a chunk is split over nsp adjacent lanes, each with
+// 1, 2 or 4 of its runs of obstacles; the nsp partial sums meet by wave
 // shuffles.
 // ---------------------------------------------------------------------------
 template <int MODEL, int S, int PT, bool IND, bool MAP, bool FIELD>
@@ -1202,7 +1250,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     }
     lds_barrier();
     // the largest |o|^2 over the obstacles (non-negative floats order as
-    // their bit patterns); read in phase 5
+    // their bit patterns); read in phase 6
     if constexpr (PT != 0) {
         if (omax_mine > 0.0f) atomicMax(L.omax, __float_as_int(omax_mine));
     }
@@ -1242,7 +1290,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // What a recurrence carries from one chunk to the next, in the space of
     // the partial costs: heading and companion by chunk parity, barrier state.
     float2* carry_h = reinterpret_cast<float2*>(L.red);     // [2][kMaxTile]
-    double* carry_b = L.red + 2 * kMaxTile;
+    float* carry_b = reinterpret_cast<float*>(L.red + 2 * kMaxTile);
     static_assert(3 * kMaxTile <= kRollBlock, "carry");
 
     // the noise of sample kk at step t (Sec. IV-C mixture, scaled per Alg. 1)
@@ -1269,8 +1317,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         const float s1 = fminf(fmaxf(v1, p.u_min[1]), p.u_max[1]);
         float f0, f1;
         Model<MODEL>::inputs(p, s0, s1, f0, f1);
-        L.a[slot(idx)] = make_float4(f0, f1, 0.0f, 0.0f);
-        cost += (double)(cw0 * u.x) * (double)v0 + (double)(cw1 * u.y) * (double)v1;
+        L.a[slot(idx)] = make_float4(f0, f1, 0.0f, cw0 * u.x * v0 + cw1 * u.y * v1);
         if (keep_noise) L.nz[t * S + s] = z;
     };
 
@@ -1301,13 +1348,12 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         for (; tt < n; ++tt) step(tt, load(tt));
     };
 
-    // phase 2 (owner lanes): theta into a.z, its companion into a.y; after the
-    // last step, their terminal cost
+    // phase 2 (owner lanes): theta into a.z, its companion into a.y
     auto headings_phase = [&](int c, int n) __attribute__((always_inline)) {
-        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
+        [[maybe_unused]] const int tid = phase_tid();
         constexpr int W = Model<MODEL>::W;
         float4* a = L.a + tid;
-        double th = xs.v[2], hw = W ? xs.v[W] : 0.0f;
+        float th = xs.v[2], hw = W ? xs.v[W] : 0.0f;
         if (c > 0) {
             const float2 h = carry_h[((c - 1) & 1) * kMaxTile + tid];
             th = h.x;
@@ -1316,53 +1362,36 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         walk(
             n, [&](int tt) __attribute__((always_inline)) { return make_float2(a[tt * RS].x, a[tt * RS].y); },
             [&](int tt, float2 in) __attribute__((always_inline)) {
-                const float y = Model<MODEL>::heading((double)p.dt, th, hw, in.x, in.y);
-                a[tt * RS] = make_float4(in.x, y, (float)th, 0.0f);
+                a[tt * RS].y = Model<MODEL>::heading(p.dt, th, hw, in.x, in.y);
+                a[tt * RS].z = th;
             });
-        if (c + 1 < nch) {
-            carry_h[(c & 1) * kMaxTile + tid] = make_float2((float)th, (float)hw);
-        } else {
-            const float* rf = L.ref + T * NS;
-            const float d2 = (float)th - rf[2];
-            float f = p.Qf[2] * (d2 * d2);
-            if constexpr (W != 0) {
-                const float dw = (float)hw - rf[W];
-                f = fmaf(p.Qf[W], dw * dw, f);
-            }
-            cost += (double)f;
-        }
+        if (c + 1 < nch) carry_h[(c & 1) * kMaxTile + tid] = make_float2(th, hw);
     };
 
-    // phase 3: sines, cosines and the headings' tracking cost
-    auto sines_phase = [&](int t0, int n) __attribute__((always_inline)) {
-        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
-        constexpr int W = Model<MODEL>::W;
+    // phase 3: sines and cosines of the headings; the heading and the control
+    // cost, whose places they take, wait for the tracking cost in those of the
+    // barrier and the costmap's part
+    auto sines_phase = [&](int n) __attribute__((always_inline)) {
+        const int tid = phase_tid();
         for (int idx = tid; idx < n * S; idx += kRollBlock) {
-            float4& at = L.a[slot(idx)];
-            const float4 in = at;
+            const int at = slot(idx);
+            const float4 in = L.a[at];
             float sn, cn;
             heading_sincos(in.z, sn, cn);
-            const float* rf = L.ref + (t0 + idx / S + 1) * NS;
-            const float d2 = in.z - rf[2];
-            float c = p.Q[2] * (d2 * d2);
-            if constexpr (W != 0) {
-                const float dw = in.y - rf[W];
-                c = fmaf(p.Q[W], dw * dw, c);
-            }
-            cost += (double)c;
-            at = make_float4(in.x, in.y, sn, cn);
+            L.a[at] = make_float4(in.x, in.y, sn, cn);
+            L.b[at] = in.z;
+            L.mp[at] = in.w;
         }
     };
 
-    // phase 4 (lanes 0..2S-1): positions and velocities; after the last step,
-    // their terminal cost
+    // phase 4 (lanes 0..2S-1): positions and velocities
     auto positions_phase = [&](int c, int n) __attribute__((always_inline)) {
         [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
         const int axis = tid / S;
         const float4* a = L.a + s_mine;
         float* pos = (axis == 0 ? L.px : L.py) + s_mine;
         [[maybe_unused]] float* vel = (axis == 0 ? L.vx : L.vy) + s_mine;
-        double q = 0.0, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
+        float q = 0.0f, v = MODEL == MPPI_CAR ? xs.v[3] : axis == 0 ? xs.v[3] : xs.v[4];
         float th = xs.v[2];
         if (c > 0) {        // (this lane's own last step of the chunk before)
             const float2 h = carry_h[((c - 1) & 1) * kMaxTile + s_mine];
@@ -1379,48 +1408,46 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 Model<MODEL>::position(p, axis, q, v, in.x, in.y, sn, cs);
                 sn = in.z;
                 cs = in.w;
-                pos[tt * RS] = (float)q;
-                if constexpr (NS > 4) vel[tt * RS] = (float)v;
+                pos[tt * RS] = q;
+                if constexpr (NS > 4) vel[tt * RS] = v;
             });
-        if (c + 1 == nch) {
-            const float* rf = L.ref + T * NS;
-            const float d0 = (float)q - rf[axis];
-            float f = p.Qf[axis] * (d0 * d0);
-            if constexpr (NS > 4) {
-                const float d3 = (float)v - rf[3 + axis];
-                f = fmaf(p.Qf[3 + axis], d3 * d3, f);
-            }
-            cost += (double)f;
-        }
     };
 
-    // phase 5, first part: the positions' (and velocities') tracking cost
+    // phase 5: the tracking cost of every step with its control cost, one FP32
+    // sum a step over the state in order, and the terminal cost
     auto tracking_cost = [&](int t0, int n) __attribute__((always_inline)) {
-        [[maybe_unused]] const int tid = phase_tid(), s_mine = tid & (S - 1);
+        const int tid = phase_tid();
+        constexpr int W = Model<MODEL>::W;
         for (int idx = tid; idx < n * S; idx += kRollBlock) {
-            const float* rf = L.ref + (t0 + idx / S + 1) * NS;
-            const int at = slot(idx);
-            const float d0 = L.px[at] - rf[0], d1 = L.py[at] - rf[1];
-            float c = fmaf(p.Q[1], d1 * d1, p.Q[0] * (d0 * d0));
+            const int t = t0 + idx / S + 1, at = slot(idx);
+            const float* rf = L.ref + t * NS;
+            float x[NS];
+            x[0] = L.px[at];
+            x[1] = L.py[at];
+            x[2] = L.b[at];
             if constexpr (NS > 4) {
-                const float d3 = L.vx[at] - rf[3], d4 = L.vy[at] - rf[4];
-                c = fmaf(p.Q[3], d3 * d3, c);
-                c = fmaf(p.Q[4], d4 * d4, c);
+                x[3] = L.vx[at];
+                x[4] = L.vy[at];
             }
-            cost += (double)c;
+            if constexpr (W != 0) x[W] = L.a[at].y;
+            float q = 0.0f, f = 0.0f;
+#pragma unroll
+            for (int a = 0; a < NS; ++a) {
+                const float d = x[a] - rf[a], d2 = d * d;
+                q = fmaf(p.Q[a], d2, q);
+                f = fmaf(p.Qf[a], d2, f);
+            }
+            cost += (double)(q + L.mp[at]);
+            if (t == T) cost += (double)f;
         }
     };
 
-    // The barrier splits of the tile's chunks (tile_lg_pack): set by the host
-    // in the parameter block, else formed here.
-    const int lg_pack = (p.lg_pack & kLgPackSet) ? p.lg_pack : tile_lg_pack(J, T, NS, S, P);
-
-    // phase 5, second part: the fused barrier (or smallest h) of every item of
-    // chunk c, in units of one wave; then, with a costmap, map units (one item
-    // per lane, every shape point: their reads all in flight at once, away
-    // from the long obstacle units); and in chunk 0 one unit for the poses of
-    // x0 and x_d, half a wave each (as items of the list they would open one
-    // more round of full units).  The waves take units from a counter: the
+    // phase 6: the fused barrier (or smallest h) of every item of chunk c, in
+    // units of one wave; then, with a costmap, map units (one item per lane,
+    // every shape point: their reads all in flight at once, away from the long
+    // obstacle units); and in chunk 0 a unit for the poses of x0 and x_d (as
+    // items of the list they would open one more round of full units), two
+    // where each of them has 64 runs.  The waves take units from a counter: the
     // oldest wave of a SIMD wins its issue slots, so with equal shares the
     // first waves finish at 68 us of a 155 us phase (K = 16384, T = 100, 400
     // obstacles) and leave the last ones alone on their SIMDs, waiting on
@@ -1428,7 +1455,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     auto units_phase = [&](int c, int n) __attribute__((always_inline)) {
         const int lane = phase_tid() & (kWave - 1);
         const int items = n * S;
-        int lg = (lg_pack >> (c == nch - 1 ? 4 : 0)) & 15;
+        int lg = (p.lg_pack >> (c == nch - 1 ? 4 : 0)) & 15;
         [[maybe_unused]] const float* cells = nullptr;
         if constexpr (FIELD) {
             // enough lanes per item to give every wave a unit
@@ -1436,9 +1463,22 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
             lg = 0;
             while (lg < kFieldLgMax && items << lg <= (kRollWaves - 1) * kWave) ++lg;
         }
-        const int ounits = ((items << lg) + kWave - 1) / kWave;
+        int ounits = ((items << lg) + kWave - 1) / kWave, xunits = (!IND && c == 0) ? 1 : 0;
+        // The obstacles' runs (set_splits): the steps and the units at which the
+        // second and the third part of the horizon begin in this chunk.
+        constexpr bool RUNS = !IND && !FIELD;
+        [[maybe_unused]] int s1 = 0, s2 = 0, u1 = 0, u2 = 0;
+        if constexpr (RUNS) {
+            const int t0 = c * tc;
+            s1 = min(max((p.run_steps & 0xFFFF) - t0, 0), n);
+            s2 = min(max((p.run_steps >> 16) - t0, s1), n);
+            u1 = ((s1 * S << run_lanes(p.run_lg, 0)) + kWave - 1) / kWave;
+            u2 = u1 + (((s2 - s1) * S << run_lanes(p.run_lg, 1)) + kWave - 1) / kWave;
+            ounits = u2 + (((n - s2) * S << run_lanes(p.run_lg, 2)) + kWave - 1) / kWave;
+            if (c == 0) xunits = ((kXSlots << run_split(p.run_lg, 0)) + kWave - 1) / kWave;
+        }
         const int munits = MAP ? (items + kWave - 1) / kWave : 0;
-        const int units = ounits + munits + ((!IND && c == 0) ? 1 : 0);
+        const int units = ounits + munits + xunits;
         [[maybe_unused]] float omax2 = 0.0f;
         if constexpr (PT != 0) omax2 = uniform(2.0f * __int_as_float(*L.omax));
         auto pose_of = [&](int at) __attribute__((always_inline)) {
@@ -1470,29 +1510,38 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         for (int u = next_unit(); u < units; u = next_unit()) {
             // lane `sp` of the item's 2^lg: neighbouring lanes (one run of
             // obstacles in LDS), with the far field lanes 64 / 2^lg apart
-            int lgu = lg, item, sp, at;
+            int lgu = lg, item, sp, at, end = items;
+            [[maybe_unused]] int rlg = 0;
             if (FIELD && u < ounits) {
                 const int per = kWave >> lg;
                 item = u * per + (lane & (per - 1));
                 sp = lane >> (6 - lg);
             } else {
-                item = (u * kWave + lane) >> lg;
-                sp = lane & ((1 << lg) - 1);
+                int ul = u, first = 0;
+                if constexpr (RUNS) {
+                    const int part = u < u1 ? 0 : u < u2 ? 1 : 2;
+                    lgu = run_lanes(p.run_lg, part);
+                    rlg = run_split(p.run_lg, part);
+                    ul -= part == 0 ? 0 : part == 1 ? u1 : u2;
+                    first = (part == 0 ? 0 : part == 1 ? s1 : s2) * S;
+                    end = (part == 0 ? s1 : part == 1 ? s2 : n) * S;
+                }
+                item = first + ((ul * kWave + lane) >> lgu);
+                sp = lane & ((1 << lgu) - 1);
             }
-            int end = items;
             if (u >= ounits) {
-                const bool ends = u == ounits + munits;
+                const bool ends = u >= ounits + munits;
                 if constexpr (MAP) {
-                    const int it = ends ? lane : (u - ounits) * kWave + lane;
+                    const int it = !ends ? (u - ounits) * kWave + lane : u == ounits + munits ? lane : kXSlots;
                     if (it < (ends ? kXSlots : items)) {
                         const int ma = ends ? n * RS + it : in_order(it);
                         L.mp[ma] = map_terms<PT, IND>(p, P, pose_of(ma), inv_res, offx, offy);
                     }
                 }
                 if (!ends) continue;
-                lgu = 5;
-                item = lane >> 5;
-                sp = lane & 31;
+                lgu = RUNS ? rlg = run_split(p.run_lg, 0) : 5;
+                item = ((u - ounits - munits) * kWave + lane) >> lgu;
+                sp = lane & ((1 << lgu) - 1);
                 end = kXSlots;
                 at = n * RS + item;
             } else {
@@ -1517,8 +1566,8 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                     }
                 }
                 if (walk_all) {
-                    if constexpr (PT == 0 || FIELD) part = walk_points<IND>(p, L, P, pose, sp, lgu);
-                    else part = fused_barrier_pose<MODEL, PT>(p, L, sa2, sb2, ss, pose, sp, lgu, omax2);
+                    if constexpr (!RUNS) part = walk_points<IND>(p, L, P, pose, sp, lgu);
+                    else part = fused_barrier_pose<MODEL, PT>(p, L, sa2, sb2, ss, pose, sp, lgu, rlg, omax2);
                 }
             }
             const int step = FIELD && u < ounits ? kWave >> lgu : 1;
@@ -1536,23 +1585,21 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         if constexpr (MAP) b = IND ? fminf(b, L.mp[idx]) : b + L.mp[idx];
         return b;
     };
-    // barrier-state recursion over chunk c (owner lanes) and its cost, in FP64
-    // (a body in contact has barriers of 1e4 and more, where FP32 rounds the
-    // state by what separates the samples); with the indicator, the weight of
-    // every step that violates a constraint
+    // barrier-state recursion over chunk c (owner lanes) and its cost; with the
+    // indicator, the weight of every step that violates a constraint
     auto beta_phase = [&](int c, int n) __attribute__((always_inline)) {
         const int tid = phase_tid();
-        const double g = (double)p.gamma_b, w = IND ? (double)p.collision_weight : (double)p.r_b;
-        double beta = 0.0;
-        if constexpr (!IND) beta = c == 0 ? (double)barrier_at(n * RS) : carry_b[tid];      // (from beta_0)
+        const float w = IND ? p.collision_weight : p.r_b;
+        float beta = 0.0f;
+        if constexpr (!IND) beta = c == 0 ? barrier_at(n * RS) : carry_b[tid];      // (from beta_0)
         walk(
             n, [&](int tt) __attribute__((always_inline)) { return barrier_at(tt * RS + tid); },
             [&](int, float b) __attribute__((always_inline)) {
                 if constexpr (IND) {
-                    cost += b < 0.0f ? w : 0.0;
+                    cost += (double)(b < 0.0f ? w : 0.0f);
                 } else {
-                    beta = fma(g, beta, (double)b);
-                    cost = fma(w, beta, cost);
+                    beta = fmaf(p.gamma_b, beta, b);
+                    cost += (double)(w * beta);
                 }
             });
         if (!IND && c + 1 < nch) carry_b[tid] = beta;
@@ -1571,7 +1618,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         if (tid == kRollBlock - 1) L.next[(c + 1) & 1] = 0;
         if (owner) headings_phase(c, n);
         lds_barrier();
-        sines_phase(t0, n);
+        sines_phase(n);
         if (!IND && c == 0 && tid >= kRollBlock - kXSlots) {
             // beta_0 and beta_d are the fused barriers of the poses of x0 and
             // x_d = x_ref[T], carried in chunk 0's two extra slots
@@ -1587,6 +1634,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
         if (tid < 2 * S) positions_phase(c, n);
         lds_barrier();
         tracking_cost(t0, n);
+        lds_barrier();          // (the units write over the headings)
         units_phase(c, n);
         lds_barrier();
     }

@@ -67,8 +67,10 @@ struct DevParams {
     int32_t cost_mode;       // MPPI_COST_DBAS or MPPI_COST_INDICATOR (no barrier state)
     float collision_weight;  // weight of the collision indicator
     int32_t shape_kind;      // ShapeForm: the layout form the model's fixed-P tile may use
-    int32_t lg_pack;         // the rollout's barrier splits (tile_lg_pack | kLgPackSet), or 0:
-                             //   the kernel forms them itself
+    int32_t lg_pack;         // the rollout's barrier splits (set_splits): lanes per item of the chunks
+                             //   before the last, and of the last
+    int32_t run_lg;          // the obstacles' runs: their splits and lanes per item, by part
+    int32_t run_steps;       // the first steps of the second and the third part
     double beta_d_weight;    // R_B sum_{t=1..T} c_t / beta_d, the common barrier-state cost per unit of beta_d
     const float* sgf_coef;   // [T][2m+1] smoothing weights of step t over its window
     const float* obs;        // [J][3] cx, cy, r (world frame)
@@ -363,15 +365,58 @@ __host__ __device__ inline int tile_split_lg(int items, int J, int P)
     return lg;
 }
 
-constexpr int kLgPackSet = 1 << 12;
-
-// The splits of a tile's chunks (all but the last have one length), packed 4
-// bits each, with kLgPackSet.
-__host__ __device__ inline int tile_lg_pack(int J, int T, int n, int S, int P)
+// A walk over all obstacles adds a pose's up in 2^rlg runs, run i taking
+// obstacles i, i + 2^rlg, ..., and then the runs' sums in pairs, neighbours
+// first.  The sum is FP32, so a body in contact (barriers of 1e4 and more) has
+// costs that depend on rlg by more than separates the samples: rlg is part of
+// a controller's results, and is chosen apart from the lanes that share an item
+// (2^lanes of them, each with up to four runs), which only cost time.  Three
+// parts of the horizon have a split each: about its first tenth, and what
+// follows in chunks of the acceptance rule with a shorter last one.  A part's
+// split is the one whose units of a chunk, spread over the CU's four SIMDs,
+// would cost least with a lane per run, among those with a unit for every wave
+// that owns no sample.
+__host__ __device__ inline int run_split_lg(int items, int J, int P, int DW)
 {
-    const int tc = tile_chunk(J, T, n, S);
-    const int last = T - (T - 1) / tc * tc;
-    return kLgPackSet | tile_split_lg(tc * S, J, P) | tile_split_lg(last * S, J, P) << 4;
+    int lg = 0;
+    long best = -1;
+    for (int l = 0; l <= 6 && (1 << l) <= (J > 1 ? J : 1); ++l) {
+        const long units = ((long)items * (1L << l) + kWave - 1) / kWave;
+        if (units < kRollBlock / kWave - DW) {
+            if (best < 0) lg = l;                        // the finest so far
+            continue;
+        }
+        const long per_lane = (J + (1 << l) - 1) >> l;
+        const long cost = (units + 3) / 4 * (per_lane * P + 8);
+        if (best < 0 || cost < best) {
+            best = cost;
+            lg = l;
+        }
+    }
+    return lg;
+}
+
+__host__ __device__ inline int run_split(int run_lg, int part) { return (run_lg >> (4 * part)) & 15; }
+__host__ __device__ inline int run_lanes(int run_lg, int part) { return (run_lg >> (4 * part + 12)) & 15; }
+
+// The splits of a controller's tiles, into its parameter block.
+inline void set_splits(DevParams& p)
+{
+    const int J = p.J, T = p.T, S = p.spt, P = p.P;
+    const int tc = tile_chunk(J, T, p.n, S), last = T - (T - 1) / tc * tc;
+    const int lg[2] = {tile_split_lg(tc * S, J, P), tile_split_lg(last * S, J, P)};
+    p.lg_pack = lg[0] | lg[1] << 4;
+    const int ac = tile_chunk_steps(J, T, p.n, S) > 0 ? tile_chunk_steps(J, T, p.n, S) : 1;
+    const int c0 = (T + 9) / 10 < ac ? (T + 9) / 10 : ac, DW = (S + kWave - 1) / kWave;
+    const int third = T > c0 ? T - ((T - c0 - 1) % ac + 1) : T;
+    const int steps[3] = {c0, ac, T - third};
+    p.run_lg = 0;
+    for (int i = 0; i < 3; ++i) {
+        const int r = run_split_lg(steps[i] * S, J, P, DW);
+        const int l = lg[0] > r ? r : lg[0] < r - 2 ? r - 2 : lg[0];
+        p.run_lg |= r << (4 * i) | l << (4 * i + 12);
+    }
+    p.run_steps = c0 | third << 16;
 }
 
 // Dynamic LDS bytes one rollout tile of this controller needs.

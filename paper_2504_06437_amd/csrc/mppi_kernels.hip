@@ -178,21 +178,21 @@ constexpr int kExpBlock = 256;
 template <int MODEL>
 __device__ void explore_poses(const DevParams& p, const X0& xs, float4* pose)
 {
-    double th = xs.v[2], hw = Model<MODEL>::W ? xs.v[Model<MODEL>::W] : 0.0f;
-    double q[2] = {0.0, 0.0}, v[2] = {xs.v[3], MODEL == MPPI_CAR ? xs.v[3] : xs.v[4]};
+    float th = xs.v[2], hw = Model<MODEL>::W ? xs.v[Model<MODEL>::W] : 0.0f;
+    float q[2] = {0.0f, 0.0f}, v[2] = {xs.v[3], MODEL == MPPI_CAR ? xs.v[3] : xs.v[4]};
     float sth, cth;
-    heading_sincos((float)th, sth, cth);
+    heading_sincos(th, sth, cth);
     pose[0] = make_float4(0.0f, 0.0f, cth, sth);
     for (int t = 0; t < p.T; ++t) {
         const float s0 = fminf(fmaxf(p.Ustar[2 * t], p.u_min[0]), p.u_max[0]);
         const float s1 = fminf(fmaxf(p.Ustar[2 * t + 1], p.u_min[1]), p.u_max[1]);
         float f0, f1;
         Model<MODEL>::inputs(p, s0, s1, f0, f1);
-        const float y = Model<MODEL>::heading((double)p.dt, th, hw, f0, f1);
+        const float y = Model<MODEL>::heading(p.dt, th, hw, f0, f1);
         Model<MODEL>::position(p, 0, q[0], v[0], f0, y, sth, cth);
         Model<MODEL>::position(p, 1, q[1], v[1], f0, y, sth, cth);
-        heading_sincos((float)th, sth, cth);
-        pose[t + 1] = make_float4((float)q[0], (float)q[1], cth, sth);
+        heading_sincos(th, sth, cth);
+        pose[t + 1] = make_float4(q[0], q[1], cth, sth);
     }
 }
 
@@ -790,7 +790,7 @@ hipError_t launch_rollout(const DevParams& p0, const StepArgs& a, hipStream_t s)
 {
     DevParams p = p0;
     if (!tile_samples_supported(p.spt)) return hipErrorInvalidValue;
-    p.lg_pack = tile_lg_pack(p.J, p.T, p.n, p.spt, p.P);
+    set_splits(p);
     const size_t lds = tile_lds_bytes(p.J, p.T, p.n, p.spt);
     switch (p.model) {
     case MPPI_QUAD6: return launch_rollout_quad6(p, a, lds, s);
