@@ -11,6 +11,10 @@
 // exactly as before.  A query outside the grids, or in a cell whose near list
 // is full, walks all obstacles.
 //
+// The polynomials are of 1/h itself, and the barrier is 1/max(h, h_eps): an
+// obstacle with an h below h_eps anywhere in a cell is near there, however far
+// it lies.
+//
 // Near and far are told apart by the polynomial's error: an obstacle whose
 // edge lies kappa half-widths W beyond the cell leaves a relative error of at
 // most about 8 (kappa + 1)^-9.25 (measured over radii from 0.05 W to 5 W), and
@@ -98,6 +102,6 @@ inline float field_margin(int model, int P, int32_t shape_kind, int32_t cost_mod
 }
 
 // Device memory of a field, and its build on a stream (one kernel).
-hipError_t launch_field(const float* d_obs, int J, float margin, void* d_field, hipStream_t s);
+hipError_t launch_field(const float* d_obs, int J, float margin, float h_eps, void* d_field, hipStream_t s);
 
 }  // namespace dbas

@@ -462,13 +462,15 @@ __device__ FieldLevel field_level(int l, double cx, double cy, double w, double 
 }
 
 // Terms of an obstacle at (x, y) from a cell's centre, for the choice of
-// kappa: its edge's distance beyond the cell in half-widths, and its term at
-// the centre.
-__device__ __forceinline__ float field_kappa(float x, float y, float r, float W, float& f)
+// kappa: its edge's distance beyond the cell in half-widths (below every
+// threshold where the cell's smallest h is below h_eps), and its term at the
+// centre.
+__device__ __forceinline__ float field_kappa(float x, float y, float r, float W, float h_eps, float& f)
 {
     const float dx = fmaxf(fabsf(x) - W, 0.0f), dy = fmaxf(fabsf(y) - W, 0.0f);
+    const float d2 = fmaf(dx, dx, dy * dy);
     f = __builtin_amdgcn_rcpf(fmaf(x, x, fmaf(y, y, -r * r)));
-    return (sqrtf(fmaf(dx, dx, dy * dy)) - r) * __builtin_amdgcn_rcpf(W);
+    return fmaf(-r, r, d2) >= h_eps ? (sqrtf(d2) - r) * __builtin_amdgcn_rcpf(W) : -1.0f;
 }
 
 // One workgroup per macro cell of 4 x 4 cells.  The obstacles far from the
@@ -476,8 +478,8 @@ __device__ __forceinline__ float field_kappa(float x, float y, float r, float W,
 // it, which each of its cells takes over by its values at the cell's nodes, so
 // a cell itself sums only the obstacles around its macro cell: about 40 of 400
 // where every cell summing them all took eight times the work.
-__global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restrict__ obs, int J, float margin, FieldHeader* hdr,
-                                                       float* __restrict__ cells)
+__global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restrict__ obs, int J, float margin, float h_eps,
+                                                       FieldHeader* hdr, float* __restrict__ cells)
 {
     // per obstacle: the macro-far ones, macro-centred (near ones: at infinity),
     // then in their place the macro-near ones (with r); the obstacles; the
@@ -588,7 +590,7 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
         const float3 o = sobs[j];
         const float x = (float)((double)o.x - mcx), y = (float)((double)o.y - mcy);
         float f;
-        const float k = field_kappa(x, y, o.z, MW, f);
+        const float k = field_kappa(x, y, o.z, MW, h_eps, f);
         add_errors(k, f, err, far);
     }
     __shared__ float skap[kFieldWaves][2 * kKappas];
@@ -615,7 +617,7 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
         const float3 o = sobs[j];
         const float x = (float)((double)o.x - mcx), y = (float)((double)o.y - mcy), r = o.z;
         float f;
-        so[j] = field_kappa(x, y, r, MW, f) >= mk ? make_float4(x, y, -r * r, 0.0f) : away;
+        so[j] = field_kappa(x, y, r, MW, h_eps, f) >= mk ? make_float4(x, y, -r * r, 0.0f) : away;
     }
     __syncthreads();
     if (wave == 0) {
@@ -701,7 +703,7 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 float f;
-                const float k = field_kappa(o.x - cx[c], o.y - cy[c], o.w, W, f);
+                const float k = field_kappa(o.x - cx[c], o.y - cy[c], o.w, W, h_eps, f);
                 add_errors(k, f, e[c], fr[c]);
             }
         }
@@ -737,7 +739,7 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
             if (lane < n) {
                 const float4 o = sn[i0 + lane];
                 float f;
-                near = !(field_kappa(o.x - cx[c], o.y - cy[c], o.w, W, f) >= ck[c]);
+                near = !(field_kappa(o.x - cx[c], o.y - cy[c], o.w, W, h_eps, f) >= ck[c]);
             }
             const uint64_t m = __ballot(near);
             const int at = cnt[c] + __popcll(m & ((1ull << lane) - 1ull));
@@ -776,11 +778,12 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
 
 }  // namespace
 
-hipError_t launch_field(const float* d_obs, int J, float margin, void* d_field, hipStream_t s)
+hipError_t launch_field(const float* d_obs, int J, float margin, float h_eps, void* d_field, hipStream_t s)
 {
     if (J < 1 || J > MPPI_JMAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_field, dim3(kFieldMacros), dim3(kFieldBlock), ((size_t)J * 30 + 15) & ~(size_t)15, s, d_obs, J, margin,
-                       static_cast<FieldHeader*>(d_field), reinterpret_cast<float*>(static_cast<char*>(d_field) + 256));
+                       h_eps, static_cast<FieldHeader*>(d_field),
+                       reinterpret_cast<float*>(static_cast<char*>(d_field) + 256));
     return hipGetLastError();
 }
 

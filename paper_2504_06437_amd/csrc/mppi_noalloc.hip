@@ -153,7 +153,8 @@ extern "C" int mppi_step_noalloc(const mppi_config* cfg, const mppi_problem* pro
     a.counter = counter;
     a.S_e = S_e;
     if (field_wanted(p.model, p.K, p.T, p.J, p.P, p.shape_kind, p.cost_mode)) {
-        e = launch_field(p.obs, p.J, field_margin(p.model, p.P, p.shape_kind, p.cost_mode, p.shape), field_mem, s);
+        e = launch_field(p.obs, p.J, field_margin(p.model, p.P, p.shape_kind, p.cost_mode, p.shape), p.h_eps,
+                         field_mem, s);
         p.field = static_cast<const FieldHeader*>(field_mem);
     }
     if (e == hipSuccess) e = launch_rollout(p, a, s);

@@ -659,7 +659,7 @@ extern "C" int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int3
     ++h->version;
     if (field_wanted(h->p.model, h->cfg.K, h->cfg.T, J, h->p.P, h->p.shape_kind, h->p.cost_mode)) {
         if (!h->d_field) HIP_TRY(h, hipMalloc(&h->d_field, kFieldBytes));
-        HIP_TRY(h, launch_field(h->d_obs, J, h->field_margin(), h->d_field, h->stream));
+        HIP_TRY(h, launch_field(h->d_obs, J, h->field_margin(), h->p.h_eps, h->d_field, h->stream));
         h->p.field = static_cast<const FieldHeader*>(h->d_field);
     }
     return h->retile();
