@@ -518,9 +518,11 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
     float b[4] = {INFINITY, INFINITY, INFINITY, INFINITY};      // min x, -max x, min y, -max y
     bool bad = false;
     for (int j = tid; j < J; j += kFieldBlock) {
-        const float x = obs[3 * j], y = obs[3 * j + 1], r = obs[3 * j + 2];
+        // (the walk squares r: a negative radius in device memory, which the
+        // host cannot check, is its magnitude here too)
+        const float x = obs[3 * j], y = obs[3 * j + 1], r = fabsf(obs[3 * j + 2]);
         sobs[j] = make_float3(x, y, r);
-        bad |= !(fabsf(x) < 1e8f && fabsf(y) < 1e8f && fabsf(r) < 1e8f);
+        bad |= !(fabsf(x) < 1e8f && fabsf(y) < 1e8f && r < 1e8f);
         b[0] = fminf(b[0], x);
         b[1] = fminf(b[1], -x);
         b[2] = fminf(b[2], y);

@@ -1,10 +1,12 @@
 """The obstacles' far field at the edges of what it accepts, against the oracle
 to the parity tests' own tolerances: a barrier cap h_eps that binds for
-obstacles far beyond a cell."""
+obstacles far beyond a cell, and radii that only the device holds."""
+import numpy as np
 import pytest
 
 from parity_checks import check
 from test_gpu_field import TRACTOR, _step
+from paper_2504_06437_amd import _lib as A
 from paper_2504_06437_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +31,25 @@ def test_cap_binds_beyond_the_cell(body, h_eps):
     1e6 caps them all (every list is full: the poses walk)."""
     g, ref, p = _step(_world(body), h_eps=h_eps)
     check(g, ref, p, what=f"{body} h_eps {h_eps}")
+
+
+@pytest.mark.parametrize("body", ["quadrotor", "vehicle"])
+def test_radii_on_the_device_count_by_their_magnitude(body):
+    """h = |p - c|^2 - r^2 does not see the sign of r, and device memory is not
+    checked: the same costs with some radii negated, bit for bit."""
+    from paper_2504_06437_amd.controller import Controller
+    from paper_2504_06437_amd.hip import DeviceArray
+    wl = _world(body)
+    c = Controller(dict(wl["params"], tile_samples=32))
+    c.load_workload(wl)
+    costs = []
+    for sign in (1.0, -1.0):
+        obs = wl["obstacles"].copy()
+        obs[::3, 2] *= np.float32(sign)
+        d = DeviceArray.from_numpy(obs)
+        assert c.L.mppi_set_obstacles(c.h, len(obs), d.ptr, A.MEM_DEVICE) == A.OK
+        c.set_state({"counter": 0, "S_e": 1.0, "U": wl["U0"]})
+        c.step(wl["x0"])
+        costs.append(c.costs())
+    c.close()
+    np.testing.assert_array_equal(costs[1], costs[0])
