@@ -758,6 +758,11 @@ int mppi_ctrl::launch_step(const float* x0_host, const float* x0_dev, float* u0_
     a.mark = mark ? 1u : 0u;
     a.seq = (uint32_t)(iter + 1);
     plan_ready = false;
+    if (!mark && !captured) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_TRY(this, hipStreamIsCapturing(stream, &cap));
+        captured = cap != hipStreamCaptureStatusNone;
+    }
     if (x0_host) std::memcpy(a.x0, x0_host, sizeof(float) * p.n);
     a.x0_ptr = x0_dev;
     a.u0_dev = u0_dev;
@@ -832,7 +837,7 @@ extern "C" int mppi_step(mppi_t* h, const float* x0, float* u0)
     // back to the synchronisation -- which also reports errors -- after 50 ms
     if (!wait_completion(h->h_res, h->iter)) HIP_TRY(h, hipStreamSynchronize(h->stream));
     h->stage_used = 0;          // every upload came before the step
-    h->plan_ready = true;
+    h->plan_ready = !h->captured;
     const HostResult* r = h->h_res;
     u0[0] = r->u0[0];
     u0[1] = r->u0[1];

@@ -30,6 +30,8 @@ struct mppi_ctrl {
     size_t sdf4_bytes = 0;
     dbas::HostResult* h_res = nullptr;   // pinned: the result block, the plan [T][2], the staging
     bool plan_ready = false;             // the last iteration was a synchronous step: its U* is there
+    bool captured = false;               // a graph holds iterations of this controller: the host does
+                                         //   not see its launches, and no longer knows which was last
     // Pinned staging of the host's inputs: an upload takes the next bytes of it
     // and a kernel on the stream fetches them, so neither call nor caller waits.
     // The bytes are free again once the stream is known to be past the kernel

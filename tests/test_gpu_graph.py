@@ -1,0 +1,68 @@
+"""Iterations a caller captures into a graph of its own: what the handle reports
+after a replay, which the host does not see, is what ran last."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2504_06437_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+class Capture:
+    """A graph of what is issued on `stream` inside the with block."""
+
+    def __init__(self, stream):
+        from paper_2504_06437_amd import hip
+        self.hip, self.stream = hip.runtime(), ctypes.c_void_p(stream)
+        self.graph, self.exec = ctypes.c_void_p(), ctypes.c_void_p()
+
+    def __enter__(self):
+        assert self.hip.hipStreamBeginCapture(self.stream, 1) == 0      # thread-local
+        return self
+
+    def __exit__(self, kind, *_):
+        assert self.hip.hipStreamEndCapture(self.stream, ctypes.byref(self.graph)) == 0
+        if kind is None:
+            assert self.hip.hipGraphInstantiate(ctypes.byref(self.exec), self.graph, None, None,
+                                                ctypes.c_size_t(0)) == 0
+
+    def replay(self):
+        assert self.hip.hipGraphLaunch(self.exec, self.stream) == 0
+        assert self.hip.hipStreamSynchronize(self.stream) == 0
+
+    def close(self):
+        self.hip.hipGraphExecDestroy(self.exec)
+        self.hip.hipGraphDestroy(self.graph)
+
+
+def test_plan_after_a_replay_is_the_replays():
+    """Two iterations in a graph (the warm start's halves return to their
+    places), replayed between pairs of synchronous steps: U* is the eager
+    controller's every time."""
+    from paper_2504_06437_amd.controller import Controller
+    from paper_2504_06437_amd.hip import DeviceArray
+    wl = W.quad_small(K=512, T=20, J=10)
+    p = dict(wl["params"], tile_samples=16)
+    c, eager = Controller(p), Controller(p)
+    for h in (c, eager):
+        h.load_workload(wl)
+        h.step(wl["x0"])
+    x0 = DeviceArray.from_numpy(wl["x0"])
+    g = Capture(c.stream)
+    with g:
+        c.step_async(x0.at(0))
+        c.step_async(x0.at(0))
+    for _ in range(3):
+        for h in (c, eager):
+            h.step(wl["x0"])
+            h.step(wl["x0"])
+        np.testing.assert_array_equal(c.last_optimal(), eager.last_optimal())
+        g.replay()
+        eager.step_async(x0.at(0))
+        eager.step_async(x0.at(0))
+        np.testing.assert_array_equal(c.last_optimal(), eager.last_optimal())
+    g.close()
+    c.close()
+    eager.close()
