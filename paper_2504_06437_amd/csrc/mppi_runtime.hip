@@ -342,6 +342,11 @@ int mppi_ctrl::upload(void* dst, const void* src, size_t bytes)
     return MPPI_OK;
 }
 
+// After a call's uploads.  A graph of captured iterations may be launched on any
+// stream, where nothing orders it behind this one: its inputs are in place when
+// the call returns.
+int mppi_ctrl::end_upload() { return captured ? sync() : MPPI_OK; }
+
 int mppi_ctrl::read_state(CtrlState* out)
 {
     int s = sync();
@@ -662,6 +667,7 @@ extern "C" int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int3
         HIP_TRY(h, launch_field(h->d_obs, J, h->field_margin(), h->p.h_eps, h->d_field, h->stream));
         h->p.field = static_cast<const FieldHeader*>(h->d_field);
     }
+    if ((s = h->end_upload())) return s;
     return h->retile();
 }
 
@@ -721,8 +727,9 @@ extern "C" int mppi_set_reference(mppi_t* h, const float* x_ref, int32_t mem)
     const size_t cnt = (size_t)(h->cfg.T + 1) * h->p.n;
     if (mem == MPPI_MEM_HOST && !finite_all(x_ref, cnt)) return h->fail(MPPI_E_INVALID, "non-finite reference");
     if (mem != MPPI_MEM_DEVICE) {
-        const int s = h->begin_upload();
-        return s ? s : h->upload(const_cast<float*>(h->p.xref), x_ref, sizeof(float) * cnt);
+        int s = h->begin_upload();
+        if (!s) s = h->upload(const_cast<float*>(h->p.xref), x_ref, sizeof(float) * cnt);
+        return s ? s : h->end_upload();
     }
     HIP_TRY(h, hipSetDevice(h->device));
     HIP_TRY(h, hipMemcpyAsync(const_cast<float*>(h->p.xref), x_ref, sizeof(float) * cnt, hipMemcpyDeviceToDevice,

@@ -44,6 +44,7 @@ struct mppi_ctrl {
     size_t stage_used = 0;
     int begin_upload();
     int upload(void* dst, const void* src, size_t bytes);
+    int end_upload();
     // kernel timing (mppi_profile_*): event triples per recorded iteration
     bool profiling = false;
     int prof_every = 1;                    // record every n-th iteration

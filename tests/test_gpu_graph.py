@@ -28,9 +28,10 @@ class Capture:
             assert self.hip.hipGraphInstantiate(ctypes.byref(self.exec), self.graph, None, None,
                                                 ctypes.c_size_t(0)) == 0
 
-    def replay(self):
-        assert self.hip.hipGraphLaunch(self.exec, self.stream) == 0
-        assert self.hip.hipStreamSynchronize(self.stream) == 0
+    def replay(self, stream=None):
+        s = ctypes.c_void_p(stream) if stream else self.stream
+        assert self.hip.hipGraphLaunch(self.exec, s) == 0
+        assert self.hip.hipStreamSynchronize(s) == 0
 
     def close(self):
         self.hip.hipGraphExecDestroy(self.exec)
@@ -66,3 +67,37 @@ def test_plan_after_a_replay_is_the_replays():
     g.close()
     c.close()
     eager.close()
+
+
+@pytest.mark.parametrize("K,T,J", [(512, 20, 40), (8192, 64, 400)])
+def test_inputs_are_in_place_for_a_replay_on_another_stream(K, T, J):
+    """Obstacles (with and without a far field) and the reference, set between
+    replays on a stream that nothing orders behind the controller's own."""
+    from paper_2504_06437_amd.controller import Controller
+    from paper_2504_06437_amd.hip import DeviceArray, runtime
+    rng = np.random.default_rng(J)
+    wl = W.quad_large(K=K, T=T, J=J, with_map=False)
+    p = dict(wl["params"], tile_samples=32)
+    c, eager, other = Controller(p), Controller(p), Controller(p)     # other: its stream alone is used
+    x0 = DeviceArray.from_numpy(wl["x0"])
+    for h in (c, eager):
+        h.load_workload(wl)
+    g = Capture(c.stream)
+    with g:
+        c.step_async(x0.at(0))
+        c.step_async(x0.at(0))
+    for _ in range(3):
+        obs = wl["obstacles"] + np.float32([1, 1, 0]) * rng.uniform(-0.2, 0.2, (J, 3)).astype(np.float32)
+        ref = wl["x_ref"] + rng.uniform(-0.1, 0.1, wl["x_ref"].shape).astype(np.float32)
+        for h in (c, eager):
+            h.set_reference(ref)
+            h.set_obstacles(obs)
+        g.replay(other.stream)
+        eager.step_async(x0.at(0))
+        eager.step_async(x0.at(0))
+        np.testing.assert_array_equal(c.last_optimal(), eager.last_optimal())
+        np.testing.assert_array_equal(c.costs(), eager.costs())
+    runtime().hipDeviceSynchronize()
+    g.close()
+    for h in (c, eager, other):
+        h.close()
