@@ -663,9 +663,15 @@ extern "C" int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int3
     h->p.field = nullptr;
     ++h->version;
     if (field_wanted(h->p.model, h->cfg.K, h->cfg.T, J, h->p.P, h->p.shape_kind, h->p.cost_mode)) {
-        if (!h->d_field) HIP_TRY(h, hipMalloc(&h->d_field, kFieldBytes));
-        HIP_TRY(h, launch_field(h->d_obs, J, h->field_margin(), h->p.h_eps, h->d_field, h->stream));
-        h->p.field = static_cast<const FieldHeader*>(h->d_field);
+        // (without memory for the field the poses walk the obstacles)
+        if (!h->d_field && hipMalloc(&h->d_field, kFieldBytes) != hipSuccess) {
+            (void)hipGetLastError();
+            h->d_field = nullptr;
+        }
+        if (h->d_field) {
+            HIP_TRY(h, launch_field(h->d_obs, J, h->field_margin(), h->p.h_eps, h->d_field, h->stream));
+            h->p.field = static_cast<const FieldHeader*>(h->d_field);
+        }
     }
     if ((s = h->end_upload())) return s;
     return h->retile();

@@ -1,6 +1,12 @@
 """The obstacles' far field at the edges of what it accepts, against the oracle
 to the parity tests' own tolerances: a barrier cap h_eps that binds for
-obstacles far beyond a cell, and radii that only the device holds."""
+obstacles far beyond a cell, radii that only the device holds, no memory for
+the field."""
+import os
+import re
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -10,6 +16,9 @@ from paper_2504_06437_amd import _lib as A
 from paper_2504_06437_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
+
+TESTS = os.path.dirname(os.path.abspath(__file__))
+FIELD_HPP = os.path.join(os.path.dirname(TESTS), "paper_2504_06437_amd", "csrc", "mppi_field.hpp")
 
 
 def _world(body):
@@ -53,3 +62,30 @@ def test_radii_on_the_device_count_by_their_magnitude(body):
         costs.append(c.costs())
     c.close()
     np.testing.assert_array_equal(costs[1], costs[0])
+
+
+CHILD = """
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.path[:0] = sys.argv[2:4]
+from parity_checks import check
+from test_gpu_field import _step
+from paper_2504_06437_amd import workloads as W
+g, ref, p = _step(W.quad_large(K=4096, T=100, J=400, with_map=False))
+check(g, ref, p, what="no memory for the field")
+assert ctypes.c_int.in_dll(stub, "refused").value == 1
+print("walked")
+"""
+
+
+def test_without_memory_for_the_field_the_poses_walk(tmp_path):
+    """The allocation of the field alone is refused (a process whose hipMalloc
+    fails for that one size): the obstacles are set, and the step is right."""
+    macros = re.findall(r"kFieldMacros\d = (\d+)", open(FIELD_HPP).read())        # 16 cells of 64 words each
+    size = 256 + sum(int(n) for n in macros) * 16 * 64 * 4
+    stub = str(tmp_path / "fail_malloc.so")
+    subprocess.check_call(["gcc", "-shared", "-fPIC", f"-DFAIL_BYTES={size}", os.path.join(TESTS, "native", "fail_malloc.c"),
+                           "-o", stub, "-ldl"])
+    r = subprocess.run([sys.executable, "-c", CHILD, stub, TESTS, os.path.dirname(TESTS)], capture_output=True, text=True,
+                       timeout=100)
+    assert r.returncode == 0 and "walked" in r.stdout, r.stderr[-2000:]
