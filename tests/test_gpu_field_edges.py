@@ -1,7 +1,7 @@
 """The obstacles' far field at the edges of what it accepts, against the oracle
 to the parity tests' own tolerances: a barrier cap h_eps that binds for
 obstacles far beyond a cell, radii that only the device holds, no memory for
-the field."""
+the field, poses that have no cell."""
 import os
 import re
 import subprocess
@@ -26,6 +26,11 @@ def _world(body):
         return W.quad_large(K=4096, T=100, J=400, with_map=False)
     if body == "quadrotor, costmap":
         return W.quad_large(K=5700, T=61, J=400, cells=64)
+    if body == "pitch-rate quadrotor":
+        wl = W.quad_large(K=4096, T=100, J=400, with_map=False)
+        wl["params"] = dict(W.base_params("quad5", 4096, 100, 2))
+        wl["x0"], wl["x_ref"] = wl["x0"][:5], np.ascontiguousarray(wl["x_ref"][:, :5])
+        return wl
     if body == "vehicle":
         return W.car(K=6000, T=60, J=470)
     wl = W.car(K=1501, T=70, J=350)
@@ -62,6 +67,27 @@ def test_radii_on_the_device_count_by_their_magnitude(body):
         costs.append(c.costs())
     c.close()
     np.testing.assert_array_equal(costs[1], costs[0])
+
+
+@pytest.mark.parametrize("body,place", [("vehicle", "outside"), ("vehicle", "full"), ("vehicle, costmap", "full"),
+                                        ("tractor", "outside"), ("quadrotor, costmap", "full"),
+                                        ("pitch-rate quadrotor", "outside")])
+def test_poses_without_a_cell_walk(body, place):
+    """Outside the grids, and where a cell's list is full (200 obstacles within
+    half a metre, six metres off the start), a wave's poses walk the obstacles:
+    the layout forms of the paper's bodies by their own."""
+    wl = _world(body.split(",")[0] if body.startswith("vehicle") else body)
+    if body == "vehicle, costmap":
+        wl["map"] = W.quad_large(K=1, T=1, J=1, cells=64)["map"]
+    obs = wl["obstacles"].copy()
+    if place == "outside":
+        obs[:, 0] += 300.0
+    else:
+        rng = np.random.default_rng(1)
+        obs[:200, :2] = np.float32([8.0, 4.0]) + rng.uniform(-0.5, 0.5, (200, 2)).astype(np.float32)
+        obs[:200, 2] = 0.1
+    g, ref, p = _step(dict(wl, obstacles=obs))
+    check(g, ref, p, what=f"{body} {place}")
 
 
 CHILD = """
