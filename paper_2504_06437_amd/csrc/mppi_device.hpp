@@ -681,12 +681,17 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         // FMAs, the clamp and the reciprocal
         float tx[PM], ty[PM], d2[PM];
         const int P = p.P;
+        if (J == 0) return 0.0f;
 #pragma unroll
         for (int i = 0; i < PM; ++i) {
-            const float a = i < P ? p.shape[i][0] : 0.0f, b = i < P ? p.shape[i][1] : 0.0f;
-            tx[i] = fmaf(2.0f * a, cs, -(2.0f * b) * sn);
-            ty[i] = fmaf(2.0f * a, sn, (2.0f * b) * cs);
-            d2[i] = uniform(fmaf(a, a, b * b));
+            tx[i] = ty[i] = d2[i] = 0.0f;
+            if (i < P) {
+                const float a = p.shape[i][0], b = p.shape[i][1];
+                tx[i] = fmaf(2.0f * a, cs, -(2.0f * b) * sn);
+                ty[i] = fmaf(2.0f * a, sn, (2.0f * b) * cs);
+                d2[i] = uniform(fmaf(a, a, b * b));
+                asm volatile("" : "+v"(tx[i]));
+            }
         }
         return over_runs([&](int r) __attribute__((always_inline)) {
             float acc = 0.0f;
