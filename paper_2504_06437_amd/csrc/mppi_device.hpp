@@ -266,6 +266,16 @@ __device__ __forceinline__ void reciprocal_sum(const float* h, float& acc, float
     }
 }
 
+// The same of the first n >= 1 of four (the rest are not read): as one fraction
+// with the absent values 1 and their numerators 0.
+__device__ __forceinline__ float reciprocal_head(const float (&h)[4], int n)
+{
+    const float h1 = n > 1 ? h[1] : 1.0f, h2 = n > 2 ? h[2] : 1.0f, h3 = n > 3 ? h[3] : 1.0f;
+    const float ab = h[0] * h1, cd = h2 * h3;
+    const float na = n > 1 ? h[0] + h1 : 1.0f, nc = n > 3 ? h2 + h3 : n > 2 ? 1.0f : 0.0f;
+    return fmaf(na, cd, nc * ab) * __builtin_amdgcn_rcpf(ab * cd);
+}
+
 // sum_i 1/h_i of N clamped values as a value (the clamped form of the layout
 // bodies' obstacles that leave the pair-fraction form).
 template <int N>
@@ -864,10 +874,9 @@ __device__ __forceinline__ float walk_points(const DevParams& p, const TileLds& 
             if constexpr (IND) {
                 acc = fminf(acc, fminf(fminf(h[0], h[1]), fminf(h[2], h[3])));
             } else {
-                // (a point beyond the last: 1/kHMax, 1e-9)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) h[k] = k < np ? clamp_h(h[k], p.h_eps) : kHMax;
-                acc += reciprocal_total<4>(h);
+                for (int k = 0; k < 4; ++k) h[k] = clamp_h(h[k], p.h_eps);
+                acc += reciprocal_head(h, np);
             }
         }
     }
@@ -1070,10 +1079,9 @@ __device__ __forceinline__ float field_barrier_points(const DevParams& p, const 
             if constexpr (IND) {
                 near = fminf(near, fminf(fminf(h[0], h[1]), fminf(h[2], h[3])));
             } else {
-                // 1/h of an obstacle beyond the list's end: 1/kHMax (1e-9 of a term)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) h[k] = k < left ? clamp_h(h[k], p.h_eps) : kHMax;
-                near += reciprocal_total<4>(h);
+                for (int k = 0; k < 4; ++k) h[k] = clamp_h(h[k], p.h_eps);
+                near += reciprocal_head(h, left);
             }
         }
     }

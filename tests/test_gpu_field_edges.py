@@ -1,7 +1,7 @@
 """The obstacles' far field at the edges of what it accepts, against the oracle
 to the parity tests' own tolerances: a barrier cap h_eps that binds for
 obstacles far beyond a cell, radii that only the device holds, no memory for
-the field, poses that have no cell."""
+the field, poses that have no cell, and their sums far from every obstacle."""
 import os
 import re
 import subprocess
@@ -88,6 +88,29 @@ def test_poses_without_a_cell_walk(body, place):
         obs[:200, 2] = 0.1
     g, ref, p = _step(dict(wl, obstacles=obs))
     check(g, ref, p, what=f"{body} {place}")
+
+
+def test_barrier_far_from_every_obstacle():
+    """350 obstacles a kilometre off, ten points: beta_0 is 3.5e-3, and nothing
+    but its terms enters it.  Bound: 90 groups' sums in turn, each addition half
+    an ulp of FP32, 5e-6, and as much for the poses' rounding (1e-4 m in 1e3)."""
+    wl = _world("tractor")
+    obs = wl["obstacles"].copy()
+    obs[:, 0] += 1000.0
+    from paper_2504_06437_amd.controller import Controller
+    c = Controller(wl["params"])
+    c.load_workload(dict(wl, obstacles=obs))
+    c.step(wl["x0"])
+    got = c.info()["beta0"]
+    c.close()
+    x, y, th = (float(v) for v in wl["x0"][:3])
+    body = np.float32(wl["params"]["shape"]).astype(np.float64)
+    px = x + body[:, 0] * np.cos(th) - body[:, 1] * np.sin(th)
+    py = y + body[:, 0] * np.sin(th) + body[:, 1] * np.cos(th)
+    o = obs.astype(np.float64)
+    h = (px[:, None] - o[:, 0]) ** 2 + (py[:, None] - o[:, 1]) ** 2 - o[:, 2] ** 2
+    want = np.sum(1.0 / h)
+    assert abs(got - want) <= 1e-5 * want, (got, want)
 
 
 CHILD = """
