@@ -1494,8 +1494,8 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
             u1 = ((s1 * S << run_lanes(p.run_lg, 0)) + kWave - 1) / kWave;
             u2 = u1 + (((s2 - s1) * S << run_lanes(p.run_lg, 1)) + kWave - 1) / kWave;
             ounits = u2 + (((n - s2) * S << run_lanes(p.run_lg, 2)) + kWave - 1) / kWave;
-            if (c == 0) xunits = ((kXSlots << run_split(p.run_lg, 0)) + kWave - 1) / kWave;
         }
+        if (!IND && c == 0) xunits = ((kXSlots << run_split(p.run_lg, 0)) + kWave - 1) / kWave;
         const int munits = MAP ? (items + kWave - 1) / kWave : 0;
         const int units = ounits + munits + xunits;
         [[maybe_unused]] float omax2 = 0.0f;
@@ -1558,7 +1558,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                     }
                 }
                 if (!ends) continue;
-                lgu = RUNS ? rlg = run_split(p.run_lg, 0) : 5;
+                lgu = rlg = run_split(p.run_lg, 0);     // (the layout forms' beta_0 and beta_d: the same with and without a field)
                 item = ((u - ounits - munits) * kWave + lane) >> lgu;
                 sp = lane & ((1 << lgu) - 1);
                 end = kXSlots;
@@ -1591,10 +1591,9 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 // that (quadrotor K=14151 T=65, 326 obstacles within 5 m, 813
                 // against 321 us; now within 10 % in 300 drawn worlds).
                 if (walk_all) {
-                    if constexpr (RUNS) {
+                    if constexpr (FIELD) rlg = lgu;
+                    if constexpr (RUNS || PT != 0) {
                         part = fused_barrier_pose<MODEL, PT>(p, L, sa2, sb2, ss, pose, sp, lgu, rlg, omax2);
-                    } else if constexpr (PT != 0) {
-                        part = fused_barrier_pose<MODEL, PT>(p, L, sa2, sb2, ss, pose, sp, lgu, lgu, omax2);
                     } else if (VEHICLE && p.shape_kind == kShapeLayout) {
                         if constexpr (VEHICLE) {
                             float va2[8], vb2[8], vs[8];

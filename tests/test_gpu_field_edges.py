@@ -113,6 +113,23 @@ def test_barrier_far_from_every_obstacle():
     assert abs(got - want) <= 1e-5 * want, (got, want)
 
 
+@pytest.mark.parametrize("model", ["quad6", "car"])
+def test_end_poses_are_those_of_the_walk(model):
+    """beta_0 and beta_d are sums of one pose's barriers, which do not depend on
+    the samples: the same, bit for bit, with enough samples for a field and with
+    too few, in a world so dense that the goal lies inside two obstacles."""
+    from paper_2504_06437_amd.controller import Controller
+    got = []
+    for K in (4300, 70):
+        wl = W.quad_large(K=K, T=60, J=2048, with_map=False) if model == "quad6" else W.car(K=K, T=60, J=800)
+        c = Controller(dict(wl["params"], tile_samples=32))
+        c.load_workload(wl)
+        c.step(wl["x0"])
+        got.append((c.info()["beta0"], c.info()["beta_d"]))
+        c.close()
+    assert got[0] == got[1]
+
+
 CHILD = """
 import ctypes, sys
 stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
