@@ -635,10 +635,13 @@ struct AxisBody {
 // Any other shape takes the general form: h = (|e|^2 - r^2) + 2 e.d_i + |d_i|^2
 // with d_i the rotated offset, an add and two FMAs a pair.
 // (sa2, sb2) = 2 (a_i, b_i), ss = a_i^2 + b_i^2.
-template <int MODEL, int PT>
-__device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const TileLds& L, const float* sa2,
-                                                    const float* sb2, const float* ss, float4 pose, int sp, int lg,
-                                                    int rlg, float omax2)
+// In a far field's tile (FIELD) a run is a whole lane's, up to 2048 obstacles,
+// and is added up in FP64: its FP32 sum rounded to 5.2e-6 of a cost in contact
+// where the shorter runs round to 3.7e-6.
+template <int MODEL, int PT, bool FIELD, class Sum = std::conditional_t<FIELD, double, float>>
+__device__ __forceinline__ Sum fused_barrier_pose(const DevParams& p, const TileLds& L, const float* sa2,
+                                                  const float* sb2, const float* ss, float4 pose, int sp, int lg,
+                                                  int rlg, float omax2)
 {
     constexpr int PM = PT ? PT : MPPI_PMAX;
     const float eps = p.h_eps;
@@ -665,10 +668,11 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
     // The sum over this lane's runs of sum(r).
     auto over_runs = [&](auto&& sum) __attribute__((always_inline)) {
         const int n = 1 << (rlg - lg);
-        float all = 0.0f, pair = 0.0f;
+        if constexpr (FIELD) return sum(sp);
+        Sum all = 0, pair = 0;
 #pragma unroll 1
         for (int g = 0; g < n; ++g) {
-            const float w = sum(sp * n + g);
+            const Sum w = sum(sp * n + g);
             pair = (g & 1) ? pair + w : w;
             if (g < 2) all = pair;
             else if (g == 3) all += pair;
@@ -691,7 +695,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         // FMAs, the clamp and the reciprocal
         float tx[PM], ty[PM], d2[PM];
         const int P = p.P;
-        if (J == 0) return 0.0f;
+        if (J == 0) return (Sum)0;
 #pragma unroll
         for (int i = 0; i < PM; ++i) {
             tx[i] = ty[i] = d2[i] = 0.0f;
@@ -704,7 +708,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
             }
         }
         return over_runs([&](int r) __attribute__((always_inline)) {
-            float acc = 0.0f;
+            Sum acc = 0;
             run(r, [&](const float4 o) __attribute__((always_inline)) {
                 const float ex = pose.x - o.x, ey = pose.y - o.y;
                 const float ee = fmaf(ex, ex, fmaf(ey, ey, o.w));
@@ -742,7 +746,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
         auto body = [&](auto nocap_tag) __attribute__((always_inline)) {
             constexpr bool NOCAP = decltype(nocap_tag)::value;
             return over_runs([&](int r) __attribute__((always_inline)) {
-                float half = 0.0f;
+                Sum half = 0;
                 run(r, [&](const float4 o) __attribute__((always_inline)) {
                     const float ex = pose.x - o.x, ey = pose.y - o.y;
                     const float C = fmaf(ex, ex, fmaf(ey, ey, o.z));
@@ -765,9 +769,9 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
                         const float slow = 0.5f * reciprocal_total<8>(h);
                         f = g >= gmin ? f : slow;
                     }
-                    half += f;
+                    half += (Sum)f;
                 });
-                return 2.0f * half;
+                return (Sum)2 * half;
             });
         };
         const float bound = fmaf(2.0f, fmaf(pose.x, pose.x, pose.y * pose.y), omax2) + ss[0];
@@ -798,23 +802,21 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
             // takes no branch per obstacle.
             const AxisBody body(sa2, ss, pose, eps);
             return over_runs([&](int r) __attribute__((always_inline)) {
-                float half = 0.0f;
+                Sum half = 0;
                 const float4* ob = L.obs + r;
                 int i = 0;
                 for (; i + 4 <= q; i += 4) {
                     const float4 f = body.four(ob[0], ob[js], ob[2 * js], ob[3 * js]);
                     ob += 4 * js;
-                    half += f.x;
-                    half += f.y;
-                    half += f.z;
-                    half += f.w;
+                    if constexpr (FIELD) half += (Sum)((f.x + f.y) + (f.z + f.w));
+                    else half = (((half + f.x) + f.y) + f.z) + f.w;
                 }
                 for (; i < q; ++i) {
-                    half += body.one(ob[0]);
+                    half += (Sum)body.one(ob[0]);
                     ob += js;
                 }
-                if (r < rem) half += body.one(ob[0]);
-                return 2.0f * half;
+                if (r < rem) half += (Sum)body.one(ob[0]);
+                return (Sum)2 * half;
             });
         }
         // (on the mirrored-axis tile o.z carries the a_0^2 offset)
@@ -822,7 +824,7 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
 #pragma unroll
         for (int i = 0; i < PM; ++i) ssx[i] = mirrored ? ss[i] - ss[0] : ss[i];
         return over_runs([&](int r) __attribute__((always_inline)) {
-            float acc = 0.0f, acc2 = 0.0f;
+            Sum acc = 0, acc2 = 0;
             run(r, [&](const float4 o) __attribute__((always_inline)) {
                 const float ex = pose.x - o.x, ey = pose.y - o.y;
                 const float ee = fmaf(ex, ex, fmaf(ey, ey, o.z));
@@ -830,7 +832,8 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
                 float h[PM];
 #pragma unroll
                 for (int i = 0; i < PM; ++i) h[i] = clamp_h(ee + fmaf(sa2[i], pu, ssx[i]), eps);
-                reciprocal_sum<PM>(h, acc, acc2);
+                if constexpr (FIELD) acc += (Sum)reciprocal_total<PM>(h);
+                else reciprocal_sum<PM>(h, acc, acc2);
             });
             return acc + acc2;
         });
@@ -844,11 +847,11 @@ __device__ __forceinline__ float fused_barrier_pose(const DevParams& p, const Ti
 // indicator: a pose violates a constraint where some h < 0; +inf without an
 // obstacle).  Four points at a time walk the obstacles: their offsets take 12
 // registers where all 16 took 48 and spilled, and four reciprocals are one.
-template <bool IND>
-__device__ __forceinline__ float walk_points(const DevParams& p, const TileLds& L, int P, float4 pose, int sp, int lg)
+template <bool IND, class Sum = std::conditional_t<IND, float, double>>
+__device__ __forceinline__ Sum walk_points(const DevParams& p, const TileLds& L, int P, float4 pose, int sp, int lg)
 {
     const int J = p.J, js = 1 << lg;
-    float acc = IND ? INFINITY : 0.0f;
+    Sum acc = IND ? (Sum)INFINITY : (Sum)0;
 #pragma unroll 1
     for (int i0 = 0; i0 < P; i0 += 4) {
         float tx[4], ty[4], ss[4];      // 2 d_i, |d_i|^2
@@ -876,7 +879,7 @@ __device__ __forceinline__ float walk_points(const DevParams& p, const TileLds& 
             } else {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) h[k] = clamp_h(h[k], p.h_eps);
-                acc += reciprocal_head(h, np);
+                acc += (Sum)reciprocal_head(h, np);
             }
         }
     }
@@ -1464,9 +1467,10 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     // phase 6: the fused barrier (or smallest h) of every item of chunk c, in
     // units of one wave; then, with a costmap, map units (one item per lane,
     // every shape point: their reads all in flight at once, away from the long
-    // obstacle units); and in chunk 0 a unit for the poses of x0 and x_d (as
-    // items of the list they would open one more round of full units), two
-    // where each of them has 64 runs.  The waves take units from a counter: the
+    // obstacle units).  Before them, in chunk 0, a unit for the poses of x0 and
+    // x_d (32 lanes each; without a far field a lane a run, two units where each
+    // has 64 runs): few lanes with long runs, whose wave taken last held the
+    // chunk up.  The waves take units from a counter: the
     // oldest wave of a SIMD wins its issue slots, so with equal shares the
     // first waves finish at 68 us of a 155 us phase (K = 16384, T = 100, 400
     // obstacles) and leave the last ones alone on their SIMDs, waiting on
@@ -1495,7 +1499,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
             u2 = u1 + (((s2 - s1) * S << run_lanes(p.run_lg, 1)) + kWave - 1) / kWave;
             ounits = u2 + (((n - s2) * S << run_lanes(p.run_lg, 2)) + kWave - 1) / kWave;
         }
-        if (!IND && c == 0) xunits = ((kXSlots << run_split(p.run_lg, 0)) + kWave - 1) / kWave;
+        if (RUNS && c == 0) xunits = ((kXSlots << run_split(p.run_lg, 0)) + kWave - 1) / kWave;
         const int munits = MAP ? (items + kWave - 1) / kWave : 0;
         const int units = ounits + munits + xunits;
         [[maybe_unused]] float omax2 = 0.0f;
@@ -1526,12 +1530,14 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
             if (lane == 0) u = atomicAdd(&L.next[c & 1], 1);
             return __builtin_amdgcn_readfirstlane(u);
         };
-        for (int u = next_unit(); u < units; u = next_unit()) {
+        for (int t = next_unit(); t < units; t = next_unit()) {
+            const int u = t - xunits;
+            const bool ends = u < 0;
             // lane `sp` of the item's 2^lg: neighbouring lanes (one run of
             // obstacles in LDS), with the far field lanes 64 / 2^lg apart
             int lgu = lg, item, sp, at, end = items;
             [[maybe_unused]] int rlg = 0;
-            if (FIELD && u < ounits) {
+            if (FIELD && !ends && u < ounits) {
                 const int per = kWave >> lg;
                 item = u * per + (lane & (per - 1));
                 sp = lane >> (6 - lg);
@@ -1548,18 +1554,17 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 item = first + ((ul * kWave + lane) >> lgu);
                 sp = lane & ((1 << lgu) - 1);
             }
-            if (u >= ounits) {
-                const bool ends = u >= ounits + munits;
+            if (ends || u >= ounits) {
                 if constexpr (MAP) {
-                    const int it = !ends ? (u - ounits) * kWave + lane : u == ounits + munits ? lane : kXSlots;
+                    const int it = !ends ? (u - ounits) * kWave + lane : t == 0 ? lane : kXSlots;
                     if (it < (ends ? kXSlots : items)) {
                         const int ma = ends ? n * RS + it : in_order(it);
                         L.mp[ma] = map_terms<PT, IND>(p, P, pose_of(ma), inv_res, offx, offy);
                     }
                 }
                 if (!ends) continue;
-                lgu = rlg = run_split(p.run_lg, 0);     // (the layout forms' beta_0 and beta_d: the same with and without a field)
-                item = ((u - ounits - munits) * kWave + lane) >> lgu;
+                lgu = rlg = RUNS ? run_split(p.run_lg, 0) : 5;
+                item = (t * kWave + lane) >> lgu;
                 sp = lane & ((1 << lgu) - 1);
                 end = kXSlots;
                 at = n * RS + item;
@@ -1567,12 +1572,14 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 at = in_order(item);
             }
             const int nsp = 1 << lgu;
-            float part = IND ? INFINITY : 0.0f;
+            // (with a far field, walks are FP64 sums until all lanes have met)
+            using Part = std::conditional_t<FIELD && !IND, double, float>;
+            Part part = IND ? (Part)INFINITY : (Part)0;
             if (item < end) {
                 const float4 pose = pose_of(at);
                 bool walk_all = true;
                 if constexpr (FIELD) {
-                    if (u < ounits) {
+                    if (!ends) {
                         bool ok;
                         if constexpr (PT == 7) {
                             if (lgu == 0) part = field_barrier_axis<0>(p, L, cells, sa2, ss, pose, sp, omax2, ok);
@@ -1593,7 +1600,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                 if (walk_all) {
                     if constexpr (FIELD) rlg = lgu;
                     if constexpr (RUNS || PT != 0) {
-                        part = fused_barrier_pose<MODEL, PT>(p, L, sa2, sb2, ss, pose, sp, lgu, rlg, omax2);
+                        part = fused_barrier_pose<MODEL, PT, FIELD>(p, L, sa2, sb2, ss, pose, sp, lgu, rlg, omax2);
                     } else if (VEHICLE && p.shape_kind == kShapeLayout) {
                         if constexpr (VEHICLE) {
                             float va2[8], vb2[8], vs[8];
@@ -1604,19 +1611,19 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
                                 vb2[i] = uniform(2.0f * b);
                                 vs[i] = uniform(fmaf(a, a, b * b));
                             }
-                            part = fused_barrier_pose<MODEL, 8>(p, L, va2, vb2, vs, pose, sp, lgu, lgu, omax2);
+                            part = fused_barrier_pose<MODEL, 8, FIELD>(p, L, va2, vb2, vs, pose, sp, lgu, lgu, omax2);
                         }
                     } else {
                         part = walk_points<IND>(p, L, P, pose, sp, lgu);
                     }
                 }
             }
-            const int step = FIELD && u < ounits ? kWave >> lgu : 1;
+            const int step = FIELD && !ends ? kWave >> lgu : 1;
             for (int m = step; m < step * nsp; m <<= 1) {
-                const float other = __shfl_xor(part, m);
+                const Part other = __shfl_xor(part, m);
                 part = IND ? fminf(part, other) : part + other;
             }
-            if (sp == 0 && item < end) L.b[at] = part;
+            if (sp == 0 && item < end) L.b[at] = (float)part;
         }
     };
 

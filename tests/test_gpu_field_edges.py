@@ -10,6 +10,8 @@ import sys
 import numpy as np
 import pytest
 
+import oracle
+from conftest import f32_params
 from parity_checks import check
 from test_gpu_field import TRACTOR, _step
 from paper_2504_06437_amd import _lib as A
@@ -114,20 +116,23 @@ def test_barrier_far_from_every_obstacle():
 
 
 @pytest.mark.parametrize("model", ["quad6", "car"])
-def test_end_poses_are_those_of_the_walk(model):
-    """beta_0 and beta_d are sums of one pose's barriers, which do not depend on
-    the samples: the same, bit for bit, with enough samples for a field and with
-    too few, in a world so dense that the goal lies inside two obstacles."""
+@pytest.mark.parametrize("K", [4300, 70])
+def test_barriers_of_the_end_poses(model, K):
+    """beta_0 and beta_d with a field (K = 4300) and without, in a world so dense
+    that the goal lies inside obstacles: 8e-7 relative, from the clamped form's
+    eight roundings and its reciprocal's ulp (6e-7 with the obstacle's own) and
+    the five additions in which 32 lanes meet."""
     from paper_2504_06437_amd.controller import Controller
-    got = []
-    for K in (4300, 70):
-        wl = W.quad_large(K=K, T=60, J=2048, with_map=False) if model == "quad6" else W.car(K=K, T=60, J=800)
-        c = Controller(dict(wl["params"], tile_samples=32))
-        c.load_workload(wl)
-        c.step(wl["x0"])
-        got.append((c.info()["beta0"], c.info()["beta_d"]))
-        c.close()
-    assert got[0] == got[1]
+    wl = W.quad_large(K=K, T=60, J=2048, with_map=False) if model == "quad6" else W.car(K=K, T=60, J=800)
+    p = dict(wl["params"], tile_samples=32)
+    c = Controller(p)
+    c.load_workload(wl)
+    c.step(wl["x0"])
+    i = c.info()
+    c.close()
+    ref = oracle.step(f32_params(dict(p, K=1)), oracle.World.from_workload(wl), wl["x0"], wl["U0"], wl["x_ref"], 1.0, 0)
+    for key in ("beta0", "beta_d"):
+        assert abs(i[key] - ref[key]) <= 8e-7 * ref[key], (key, i[key], ref[key])
 
 
 CHILD = """
