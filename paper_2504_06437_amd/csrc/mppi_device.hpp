@@ -501,28 +501,6 @@ constexpr int kFieldLgMax = 2;
 constexpr int kAhead = 8;
 constexpr int kUpdWaves = kUpdBlock / kWave;
 
-// Sum of a float pair over the block (NW waves); every thread gets it.
-template <int NW>
-__device__ __forceinline__ float2 block_sum_f2(float2 v, double* slots)
-{
-    v.x = wave_sum_f(v.x);
-    v.y = wave_sum_f(v.y);
-    float* s = reinterpret_cast<float*>(slots);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        s[2 * (threadIdx.x >> 6)] = v.x;
-        s[2 * (threadIdx.x >> 6) + 1] = v.y;
-    }
-    __syncthreads();
-    float2 r = make_float2(s[0], s[1]);
-#pragma unroll
-    for (int i = 1; i < NW; ++i) {
-        r.x += s[2 * i];
-        r.y += s[2 * i + 1];
-    }
-    return r;
-}
-
 // The quadrotor's mirrored axis with its middle point at the centre, against
 // one obstacle (see fused_barrier_pose): fast() gives half the sum of 1/h over
 // the seven points as one fraction, exact where m > 0 and f <= fcap; slow()
