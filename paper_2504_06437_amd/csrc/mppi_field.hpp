@@ -15,16 +15,18 @@
 // obstacle with an h below h_eps anywhere in a cell is near there, however far
 // it lies.
 //
-// Near and far are told apart by the polynomial's error: an obstacle whose
-// edge lies kappa half-widths W beyond the cell leaves a relative error of at
-// most about 8 (kappa + 1)^-9.25 (measured over radii from 0.05 W to 5 W), and
-// a cell takes the smallest kappa of {3.25, 4, 4.75, 6} at which the errors, each
-// times its obstacle's term, add up to at most 1.5e-7 of the far sum.  That is
-// a bound for errors of one sign at the cell's worst corner; over random
-// worlds the sum's error measured 2e-9 to 6e-9 of the whole barrier (rms), at
-// most 1e-7, below the FP32 rounding of the walk it replaces: against 64 bits
-// the costs at K = 16384, T = 100, J = 400 are 0.035 off at the 90th
-// percentile where the walk's were 0.099.
+// Near and far are told apart by an estimate of the polynomial's error: an
+// obstacle of radius r whose edge lies kappa half-widths W beyond the cell
+// leaves, in units of its term at the centre, an error of 8 (kappa + 1)^-9.25
+// times 1.5 for r -> 0, 1.1 at r = 0.2 W, 0.8 at 0.5 W, 0.3 to 0.5 at W and 0.05
+// to 0.08 at 5 W (the largest over the cell and the obstacle's direction, for
+// the kappas below).  A cell takes the smallest kappa of {3.25, 4, 4.75} at which
+// 8 (kappa + 1)^-9.25, each times its obstacle's term, adds up to at most 1.5e-7
+// of the far sum, else 6, where no sum is formed and 1.8e-7 is the most.  So the
+// far sum is off by at most 2.3e-7, and its macro cell's part by as much again,
+// were all errors of one sign at the cell's worst corner; over random worlds
+// the sum's error measured 2e-9 to 6e-9 of the whole barrier (rms), at most
+// 1e-7, below the FP32 rounding of the walk it replaces.
 #pragma once
 
 #include "mppi_internal.hpp"
@@ -40,11 +42,11 @@ constexpr int kFieldLevels = 3;
 constexpr int kMacro = 4;                           // cells per macro cell and axis
 
 // Most macro cells of each level (16 cells each): no more than 512 in all, two
-// workgroups of the build on each of 256 CUs.  The outermost grid lies a box
-// width off every obstacle: few, large cells.
+// workgroups of the build on each of 256 CUs.  The outermost grid is asked from
+// half a box width off the obstacles on: few, large cells.
 constexpr int kFieldMacros0 = 276, kFieldMacros1 = 156, kFieldMacros2 = 20;
 constexpr int kFieldMacros = kFieldMacros0 + kFieldMacros1 + kFieldMacros2;
-constexpr size_t kFieldCellBytes = (size_t)kFieldMacros * kMacro * kMacro * kFieldWords * 4;    // 2.1 MB
+constexpr size_t kFieldCellBytes = (size_t)kFieldMacros * kMacro * kMacro * kFieldWords * 4;    // 1.85 MB
 
 // One grid: lower corner, cell side, cells per axis, first record.
 struct FieldLevel {
