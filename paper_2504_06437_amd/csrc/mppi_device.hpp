@@ -1223,7 +1223,7 @@ __device__ void rollout_tile(const DevParams& p, const int tile, const X0& xs, u
     if (FIELD && tid < kFieldLevels) {
         const FieldLevel lv = p.field->level[tid];
         FieldGrid g{};
-        if (p.field->valid) {
+        if (p.field->J == J) {
             const double gx = (ox - lv.x0) / lv.side, gy = (oy - lv.y0) / lv.side;
             const double cx = fmin(fmax(floor(gx), -1e9), 1e9), cy = fmin(fmax(floor(gy), -1e9), 1e9);
             const float W = (float)(0.5 * lv.side) + p.field->margin;

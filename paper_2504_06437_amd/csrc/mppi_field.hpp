@@ -57,7 +57,9 @@ struct FieldLevel {
 struct FieldHeader {
     FieldLevel level[kFieldLevels];
     float margin;               // how far from the query the evaluated points may lie
-    int32_t valid;              // 0: no field (obstacles too far apart for FP32)
+    int32_t J;                  // the obstacles it was built for; 0: no field (too far apart for FP32, or
+                                //   the obstacles have changed).  A captured iteration holds its own count,
+                                //   and walks where this is another.
 };
 constexpr size_t kFieldBytes = 256 + kFieldCellBytes;       // header, then the records
 static_assert(sizeof(FieldHeader) <= 256, "field header");

@@ -548,12 +548,12 @@ __global__ __launch_bounds__(kFieldBlock, 4) void k_field(const float* __restric
         sh.level[tid] = field_level(tid, cx, cy, valid ? w : 1.0, valid ? hh : 1.0, J, margin);
         if (tid == 0) {
             sh.margin = margin;
-            sh.valid = valid;
+            sh.J = valid ? J : 0;
         }
     }
     __syncthreads();
     if (blockIdx.x == 0 && tid == 0) *hdr = sh;
-    if (!sh.valid) return;
+    if (sh.J == 0) return;
     int l = 0, mi = blockIdx.x;
     if (mi >= kFieldMacros0) { mi -= kFieldMacros0; l = 1; }
     if (l == 1 && mi >= kFieldMacros1) { mi -= kFieldMacros1; l = 2; }

@@ -673,6 +673,11 @@ extern "C" int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int3
             h->p.field = static_cast<const FieldHeader*>(h->d_field);
         }
     }
+    if (h->captured && h->d_field && !h->p.field) {
+        // (a graph may hold the field of the obstacles before)
+        const int32_t none = 0;
+        if ((s = h->upload(&static_cast<FieldHeader*>(h->d_field)->J, &none, sizeof none))) return s;
+    }
     if ((s = h->end_upload())) return s;
     return h->retile();
 }

@@ -5,6 +5,9 @@ import ctypes
 import numpy as np
 import pytest
 
+import oracle
+from conftest import f32_params
+from parity_checks import check, gpu_outputs
 from paper_2504_06437_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +104,31 @@ def test_inputs_are_in_place_for_a_replay_on_another_stream(K, T, J):
     g.close()
     for h in (c, eager, other):
         h.close()
+
+
+@pytest.mark.parametrize("J", [420, 40])
+def test_replay_after_another_obstacle_count(J):
+    """A graph holds its obstacle count: after 420 or 40 obstacles are set it
+    runs the first 400 of the buffer, and takes no barrier from a field that was
+    built for others.  The parity tests' own check against the oracle."""
+    from paper_2504_06437_amd.controller import Controller
+    from paper_2504_06437_amd.hip import DeviceArray
+    wl = W.quad_large(K=8192, T=64, J=450, with_map=False)
+    p = dict(wl["params"], tile_samples=32)
+    c = Controller(p)
+    x0 = DeviceArray.from_numpy(wl["x0"])
+    first = wl["obstacles"][:400]
+    c.load_workload(wl)                     # (the buffer holds 450)
+    c.set_obstacles(first)
+    g = Capture(c.stream)
+    with g:
+        c.step_async(x0.at(0))
+    new = W.quad_large(K=1, T=1, J=450, with_map=False, seed=9)["obstacles"][:J]
+    c.set_obstacles(new)
+    held = dict(wl, obstacles=np.concatenate([new[:400], first[J:]]))
+    g.replay()
+    got = gpu_outputs(c, c.last_optimal()[0], with_noise=False)
+    ref = oracle.step(f32_params(p), oracle.World.from_workload(held), wl["x0"], wl["U0"], wl["x_ref"], 1.0, 0)
+    check(got, ref, p, what=f"400 held, {J} set")
+    g.close()
+    c.close()
