@@ -207,8 +207,9 @@ void mppi_destroy(mppi_t* h);
 
 /* Circular obstacles (Sec. V-A/V-B: h = |p - c|^2 - r^2): J rows of
  * (cx, cy, r), copied.  With many of them and many samples the call also
- * starts the build of their far field on the stream.  J = 0 clears them.  Errors: INVALID (J outside
- * 0..MPPI_JMAX, non-finite or negative r). */
+ * starts the build of their far field on the stream.  J = 0 clears them.
+ * Errors: INVALID (J outside 0..MPPI_JMAX, non-finite or negative r; values in
+ * device memory are not checked, and there a radius counts by its magnitude). */
 int mppi_set_obstacles(mppi_t* h, int32_t J, const float* cxcyr, int32_t mem);
 
 /* Optional signed-distance costmap, row-major sdf[H][W] in metres, cell

@@ -71,7 +71,7 @@ static_assert(sizeof(FieldHeader) <= 256, "field header");
 // every pose; by the field a pose costs as much as the walk of j0 obstacles,
 // whatever their number.  Measured rollouts, walk against field, at K = 4096
 // (T = 50 unless said): quadrotor J = 100 35.4 / 26.9 us, T = 64 J = 64 35.3 /
-// 27.6, K = 16384 T = 100 J = 400 455 / 123; vehicle J = 100 37.1 / 42.7, J =
+// 27.6, K = 16384 T = 100 J = 400 with a costmap 455 / 112; vehicle J = 100 37.1 / 42.7, J =
 // 160 45.5 / 42.6, J = 400 84.9 / 37.4; its indicator J = 100 38.2 / 25.0,
 // J = 200 55.3 / 25.5; a ten-point body J = 160 100.9 / 44.0.  Hence us saved
 // = per_pair K T (J - j0).

@@ -83,7 +83,7 @@ struct DevParams {
                              //   other half of U (null: the other half; the handle-free entry point)
     float* Ustar;            // [T][2] optimal sequence of the last iteration (before the shift)
     float* du;               // [T][2][Kp] noise (only with export_noise)
-    float* S;                // [2][Kp] compensated cost: hi at [k], lo at [Kp + k]
+    float* S;                // [2][Kp] cost: hi at [k], lo at [Kp + k]
     float* e;                // [Kp] tile-local exponentials exp(-(S_k - rho_tile)/lambda)
     double* rho_b;           // [tiles] tile minimum cost
     double* eta_b;           // [tiles] tile sum of exponentials

@@ -1,6 +1,6 @@
 // mppi_step_noalloc: one iteration with no handle and no allocation, for
 // callers that cannot allocate device memory.  The per-iteration scratch
-// (iteration state, compensated costs, tile exponentials, tile minima,
+// (iteration state, costs, tile exponentials, tile minima,
 // normalisers and update partials) lives in one static device array per GPU;
 // its device address is taken once per device with hipGetSymbolAddress (the
 // array's name is only a host-side stand-in), and the kernels receive
